@@ -583,11 +583,14 @@ MPHX_API int mphx_gen_str_bytes(uint8_t* bytes, const uint64_t* offs, uint64_t n
 /* ---------------------------------------------------------------------------------------
  * Tuning and diagnostics.
  * mphx_set_option / mphx_get_option (process-wide):
- *   "grid"        blocks per launch of the grid-stride peeling kernels (0 = automatic: one
+ *   "grid"        blocks per launch of the peeling kernels (0 = automatic).  Up to 2^24 edges
+ *                 all rounds share one launch of at most 256 512-thread blocks (automatic: one
+ *                 per 4096 to 40960 edges), as do the assignment's layers up to 2^30 bytes of
+ *                 vertex values; above, each round is a grid-stride launch (automatic: one
  *                 256-thread block per 256 edges of the layer, between 64 and 1024).
- *   "round_batch" peeling rounds enqueued before the first check of the termination flag
- *                 (default 64; later checks come every 16 rounds).  Empty rounds past the end
- *                 cost a launch each, a check a host round trip.
+ *   "round_batch" for rounds of a launch each: peeling rounds enqueued before the first check
+ *                 of the termination flag (default 64; later checks come every 16 rounds).
+ *                 Empty rounds past the end cost a launch each, a check a host round trip.
  *   "timing"      1 = record a HIP event pair on the caller's stream around every kernel
  *                 launch of mphx_peel / mphx_mphf_build_*, accumulated per phase.
  *   "part_build"  b in 0..32 (default 21): mphx_mphf_build_* with n >= 2^b keys builds the

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "batch.h"
+#include "grid.h"
 #include "launch.h"
 #include "mphx.h"
 
@@ -169,6 +170,7 @@ struct PeelLayout {
     uint3* slots;
     void* scan;
     size_t scan_bytes;
+    GridSync* sync;
 };
 
 void layout_peel(Carve& c, uint64_t n, uint64_t m, PeelLayout& L)
@@ -185,6 +187,7 @@ void layout_peel(Carve& c, uint64_t n, uint64_t m, PeelLayout& L)
     L.tilehist = c.take<uint32_t>(hist_entries);
     L.scan_bytes = scan_scratch_bytes(hist_entries);
     L.scan = c.take<uint8_t>(L.scan_bytes);
+    L.sync = reinterpret_cast<GridSync*>(c.take<uint8_t>(run_sync_bytes()));
 }
 
 struct MphfLayout {
@@ -199,6 +202,7 @@ struct MphfLayout {
     unsigned long long* ccount;  // claim counts per round
     unsigned long long* dcount;  // update-list counts per round
     uint32_t* vals;              // static functions without claim lists: the values in layer order
+    GridSync* sync;              // over the claim counts, which such a run leaves alone
     void* scan;
     size_t scan_bytes;
 };
@@ -221,7 +225,8 @@ void layout_mphf(Carve& c, uint64_t n, uint64_t m, bool lists, MphfLayout& L, bo
     L.pairs1 = reinterpret_cast<uint2*>(region);
     L.pairs2 = reinterpret_cast<uint2*>(region ? region + 8 * n : nullptr);
     L.aux = c.take<uint8_t>(part_aux_bytes(n, m / 3, lists));
-    L.ccount = c.take<unsigned long long>(2 * (rcap + 2));
+    L.ccount = c.take<unsigned long long>(std::max<uint64_t>(2 * (rcap + 2), run_sync_bytes() / 8));
+    L.sync = reinterpret_cast<GridSync*>(L.ccount);
     L.dcount = L.ccount ? L.ccount + rcap + 2 : nullptr;
     L.claims = lists ? c.take<uint2>(m) : nullptr;
     L.claims_tmp = lists ? c.take<uint2>(m) : nullptr;
@@ -367,18 +372,47 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
     return MPHX_OK;
 }
 
+// Failures that a run's control block reports: round 0's checks, the round limit.
+int check_run_errors(const Ctrl& h, uint64_t n, uint64_t rcap, uint32_t r = 3)
+{
+    if (h.err & kErrBadEdge)
+        return fail(MPHX_EINVAL, "edge with a vertex id >= m or a repeated vertex");
+    // every degree field at most 255 and their total exactly r n: no field overflowed
+    if ((h.err & kErrDegree) || h.degsum != (uint64_t)r * n)
+        return fail(MPHX_ERANGE, "a vertex has degree above %u", MPHX_MAX_DEGREE);
+    if (h.err & kErrRounds)
+        return fail(MPHX_ERANGE, "more than %llu peeling rounds", (unsigned long long)rcap);
+    return MPHX_OK;
+}
+
+// All rounds of a run of at most kRunMaxEdges edges whose layer 0 is enqueued, then finish()
+// (enqueued after every launch of rounds; it does nothing while the peel goes on).  One host
+// read unless the peel has more rounds than a launch takes.
+template <class Finish>
+int run_rounds_grid(PeelState& st, uint32_t r, bool generic_shift, Ctrl& h, hipStream_t s, Finish finish)
+{
+    st.grid_cap = (unsigned)g_opt.grid.load();
+    for (;;) {
+        {
+            Timed t(PH_APPLY, s);
+            HIP_TRY(launch_rounds(st, r, generic_shift, s));
+        }
+        HIP_TRY(finish());
+        int rc = read_ctrl(st.ctrl, h, s);
+        if (rc) return rc;
+        rc = check_run_errors(h, st.n, st.rcap, r);
+        if (rc || h.nrounds != 0xFFFFFFFFu) return rc;
+        HIP_TRY(launch_rounds_again(st, s));
+    }
+}
+
 int check_build_errors(Ctrl* dctrl, uint64_t n, hipStream_t s, uint64_t& first_front, uint32_t r = 3)
 {
     Ctrl h;
     int rc = read_ctrl(dctrl, h, s);
     if (rc) return rc;
     first_front = h.ftail;
-    if (h.err & kErrBadEdge)
-        return fail(MPHX_EINVAL, "edge with a vertex id >= m or a repeated vertex");
-    // every degree field at most 255 and their total exactly r n: no field overflowed
-    if ((h.err & kErrDegree) || h.degsum != (uint64_t)r * n)
-        return fail(MPHX_ERANGE, "a vertex has degree above %u", MPHX_MAX_DEGREE);
-    return MPHX_OK;
+    return check_run_errors(h, n, 0, r);
 }
 
 // The round loop of an r-hypergraph peel: as run_rounds, with the r-vertex apply.
@@ -566,12 +600,14 @@ int mphx_peel(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t* order, ui
     st.lstart = L.lstart;
     st.lcount = L.lcount;
     st.ctrl = L.ctrl;
+    st.sync = L.sync;
     st.rcap = round_cap(n);
 
     HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
     HIP_TRY(launch_fill_u32(L.state, n, kUnclaimed, s));
-    HIP_TRY(launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
-    HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
+    const bool grid_run = n <= kRunMaxEdges;
+    HIP_TRY(grid_run ? launch_run_init(st, s) : launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
+    if (!grid_run) HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
     {
         Timed t(PH_BUILD, s);
         HIP_TRY(launch_edges_build(edges, n, m, L.rec, L.ctrl, s));
@@ -580,13 +616,17 @@ int mphx_peel(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t* order, ui
         Timed t(PH_FRONTIER, s);
         HIP_TRY(launch_round0(st, s));
     }
-    uint64_t f0 = 0;
-    int rc = check_build_errors(L.ctrl, n, s, f0);
-    if (rc) return rc;
-
+    uint64_t f0 = 0, peeled = 0;
     Ctrl h;
-    uint64_t peeled = 0;
-    rc = run_rounds(st, h, &peeled, s);
+    int rc;
+    if (grid_run) {
+        rc = run_rounds_grid(st, 3, false, h, s, [] { return hipSuccess; });
+        f0 = h.f0;
+        peeled = h.peeled;
+    } else {
+        rc = check_build_errors(L.ctrl, n, s, f0);
+        if (!rc) rc = run_rounds(st, h, &peeled, s);
+    }
     if (rc) return rc;
 
     {
@@ -643,12 +683,14 @@ int mphx_peel_r(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t r, uint3
     st.lstart = L.lstart;
     st.lcount = L.lcount;
     st.ctrl = L.ctrl;
+    st.sync = L.sync;
     st.rcap = round_cap(n);
 
     HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
     HIP_TRY(launch_fill_u32(L.state, n, kUnclaimed, s));
-    HIP_TRY(launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
-    HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
+    const bool grid_run = n <= kRunMaxEdges;
+    HIP_TRY(grid_run ? launch_run_init(st, s) : launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
+    if (!grid_run) HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
     {
         Timed t(PH_BUILD, s);
         HIP_TRY(launch_edges_build_r(edges, n, m, r, L.rec, L.ctrl, s));
@@ -657,12 +699,17 @@ int mphx_peel_r(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t r, uint3
         Timed t(PH_FRONTIER, s);
         HIP_TRY(launch_round0_r(st, r, s));
     }
-    uint64_t f0 = 0;
-    int rc = check_build_errors(L.ctrl, n, s, f0, r);
-    if (rc) return rc;
+    uint64_t f0 = 0, peeled = 0;
     Ctrl h;
-    uint64_t peeled = 0;
-    rc = run_rounds_r(st, r, h, &peeled, s);
+    int rc;
+    if (grid_run) {
+        rc = run_rounds_grid(st, r, true, h, s, [] { return hipSuccess; });
+        f0 = h.f0;
+        peeled = h.peeled;
+    } else {
+        rc = check_build_errors(L.ctrl, n, s, f0, r);
+        if (!rc) rc = run_rounds_r(st, r, h, &peeled, s);
+    }
     if (rc) return rc;
     {
         Timed t(PH_ORDER, s);
@@ -805,6 +852,41 @@ struct SfArgs {
     uint64_t* vals = nullptr;
 };
 
+// The values of every vertex take this much at most: all layers in one launch (launch_mphf_finish,
+// launch_sf_solve), else a launch per layer with non-temporal reads.  One launch keeps fewer
+// accesses in flight, which leaves more of a layer's values in the 256 MB memory-side cache; once
+// the values are several times its size that no longer helps.  Layers of u64 keys, one launch
+// against one per layer: 6.8 and 9.5 ms at 2^27 keys (165 MB of codes), 22.7 and 28.6 at 4x10^8,
+// 49.5 and 50.8 at 7x10^8 (861 MB), 76.9 and 74.7 at 10^9.
+constexpr uint64_t kSolveGridMaxBytes = 1ull << 30;
+
+// Assignment in reverse round order, a launch per layer; an MPHF's codes and rank samples too.
+int solve_by_layer(const PeelState& st, const MphfLayout& L, uint32_t nrounds, const SfArgs* sf, uint64_t* codes,
+                   uint64_t* rank, hipStream_t s)
+{
+    std::vector<uint64_t> lb(nrounds + 1);
+    HIP_TRY(hipMemcpyAsync(lb.data(), L.lstart, lb.size() * 8, hipMemcpyDeviceToHost, s));
+    HIP_TRY(launch_zero(L.rec, st.m * (sf ? sf_elem_bytes(mphx_sf_bits(sf->sigma)) : 1), s));
+    HIP_TRY(hipStreamSynchronize(s));
+    uint8_t* code8 = reinterpret_cast<uint8_t*>(L.rec);
+    for (int64_t r = (int64_t)nrounds - 1; r >= 0; r--) {
+        const uint64_t cnt = lb[r + 1] - lb[r];
+        Timed tm(PH_ASSIGN, s);
+        if (sf)
+            HIP_TRY(launch_sf_assign_round(L.slots + lb[r], st.vout + lb[r], cnt, sf->sigma, mphx_sf_bits(sf->sigma),
+                                           L.rec, s));
+        else
+            HIP_TRY(launch_assign_round(L.slots, L.lstart, (uint32_t)r, cnt, st.P, code8, 16384, s));
+    }
+    if (!sf) {
+        Timed tm(PH_RANK, s);
+        HIP_TRY(launch_pack_count(code8, st.m, codes, L.bcount, s));
+        const uint64_t nblocks = (st.m + 511) / 512;
+        HIP_TRY(launch_scan_u32_to_u64(L.bcount, nblocks, rank, nblocks, L.scan, L.scan_bytes, s));
+    }
+    return MPHX_OK;
+}
+
 // The MPHF (codes + rank) or, with sf, the static function (codes = its packed fields).
 int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32_t gden, uint32_t max_tries,
                uint64_t* codes, uint64_t* rank, void* ws, size_t ws_bytes, hipStream_t s, mphx_mphf_info* info,
@@ -876,20 +958,31 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
     st.ccount = L.ccount;
     st.dcount = L.dcount;
     st.aux = L.aux;
+    st.sync = L.sync;
 
     Ctrl h{};
     uint64_t peeled = 0;
     uint32_t t = 0;
-    bool done = false;
+    bool done = false, grid_run = false;
+    auto solve = [&](uint32_t nrounds) {
+        Timed tm(PH_ASSIGN, s);
+        return sf ? launch_sf_solve(st, nrounds, sf->sigma, mphx_sf_bits(sf->sigma), s)
+                  : launch_mphf_finish(st, nrounds, codes, rank, L.bcount, s);
+    };
     for (t = 0; t < max_tries; t++) {
         uint64_t sd = seed + t;
         const int pb = g_opt.part_build.load();
         const bool part = pb > 0 && n >= (1ull << pb);  // pb <= 32
         if (!part)
             HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
-        HIP_TRY(launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
-        HIP_TRY(launch_zero(L.ccount, 2 * (st.rcap + 2) * sizeof(unsigned long long), s));
-        HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
+        grid_run = !st.lists && n <= kRunMaxEdges;
+        if (grid_run) {
+            HIP_TRY(launch_run_init(st, s));
+        } else {
+            HIP_TRY(launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
+            HIP_TRY(launch_zero(L.ccount, 2 * (st.rcap + 2) * sizeof(unsigned long long), s));
+            HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
+        }
         {
             // with the partitioned build the hash only writes the edges
             Timed tm(PH_HASH, s);
@@ -921,12 +1014,21 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
             HIP_TRY(launch_round0(st, s));
         }
         uint64_t f0 = 0;
-        int rc = check_build_errors(L.ctrl, n, s, f0);
-        if (rc) {
-            if (info) { info->tries = t + 1; info->seed_used = sd; }
-            return rc;
+        int rc;
+        if (grid_run) {
+            // the rest of the build is enqueued with the rounds; it waits for a complete peel
+            rc = run_rounds_grid(st, 3, false, h, s, [&] { return solve(0); });
+            f0 = h.f0;
+            peeled = h.peeled;
+            if (rc == MPHX_ERANGE && !(h.err & kErrRounds) && info) { info->tries = t + 1; info->seed_used = sd; }
+        } else {
+            rc = check_build_errors(L.ctrl, n, s, f0);
+            if (rc) {
+                if (info) { info->tries = t + 1; info->seed_used = sd; }
+                return rc;
+            }
+            rc = st.lists ? run_rounds_lists(st, h, &peeled, s) : run_rounds(st, h, &peeled, s);
         }
-        rc = st.lists ? run_rounds_lists(st, h, &peeled, s) : run_rounds(st, h, &peeled, s);
         if (rc == kListOverflow) {  // redo this try with atomic claims
             g_opt.list_fallbacks++;
             st.lists = false;
@@ -958,21 +1060,27 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
         return fail(MPHX_ECORE, "2-core of %llu edges after %u tries", (unsigned long long)(n - peeled), max_tries);
     }
 
-    // Assignment in reverse round order with exact grids from the layer bounds.
-    std::vector<uint64_t> lb(h.nrounds + 1);
-    HIP_TRY(hipMemcpyAsync(lb.data(), L.lstart, lb.size() * 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (info) info->layer0 = h.nrounds ? lb[1] - lb[0] : 0;
+    if (info) info->layer0 = h.layer0;
+    if (!grid_run) {
+        if (info) {
+            uint64_t l0 = 0;
+            if (h.nrounds) HIP_TRY(hipMemcpyAsync(&l0, L.lstart + 1, sizeof l0, hipMemcpyDeviceToHost, s));
+            HIP_TRY(hipStreamSynchronize(s));
+            info->layer0 = l0;
+        }
+        if (m * (sf ? sf_elem_bytes(mphx_sf_bits(sf->sigma)) : 1) <= kSolveGridMaxBytes) {
+            st.grid_cap = (unsigned)g_opt.grid.load();
+            HIP_TRY(launch_sync_zero(st, s));
+            HIP_TRY(solve(h.nrounds));
+        } else {
+            int rc = solve_by_layer(st, L, h.nrounds, sf, codes, rank, s);
+            if (rc) return rc;
+        }
+    }
     if (sf) {
-        // u (one narrow element per vertex, over the records) solved layer by layer, then packed
+        // u (one narrow element per vertex, over the records) is solved; packed here
         const uint32_t b = mphx_sf_bits(sf->sigma);
         void* u = L.rec;
-        HIP_TRY(launch_zero(u, m * sf_elem_bytes(b), s));
-        HIP_TRY(hipStreamSynchronize(s));
-        for (int64_t r = (int64_t)h.nrounds - 1; r >= 0; r--) {
-            Timed tm(PH_ASSIGN, s);
-            HIP_TRY(launch_sf_assign_round(L.slots + lb[r], st.vout + lb[r], lb[r + 1] - lb[r], sf->sigma, b, u, s));
-        }
         if (sf->marks) {
             // ranked layout: marks and per-block counts, their prefix, then the fields compacted
             Timed tm(PH_RANK, s);
@@ -992,21 +1100,7 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
         g_timers.harvest();
         return MPHX_OK;
     }
-    uint8_t* code8 = reinterpret_cast<uint8_t*>(L.rec);
-    HIP_TRY(launch_zero(code8, m, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    for (int64_t r = (int64_t)h.nrounds - 1; r >= 0; r--) {
-        uint64_t cnt = lb[r + 1] - lb[r];
-        Timed tm(PH_ASSIGN, s);
-        HIP_TRY(launch_assign_round(L.slots, L.lstart, (uint32_t)r, cnt, P, code8, 16384, s));
-    }
-    {
-        Timed tm(PH_RANK, s);
-        HIP_TRY(launch_pack_count(code8, m, codes, L.bcount, s));
-        uint64_t nblocks = (m + 511) / 512;
-        HIP_TRY(launch_scan_u32_to_u64(L.bcount, nblocks, rank, nblocks, L.scan, L.scan_bytes, s));
-    }
-    HIP_TRY(hipStreamSynchronize(s));
+    if (!grid_run) HIP_TRY(hipStreamSynchronize(s));
     g_timers.harvest();
     return MPHX_OK;
 }

@@ -16,6 +16,7 @@ constexpr int kWave = 64;
 constexpr uint32_t kErrBadEdge = 1u;  // vertex id >= m or a repeated vertex in an edge
 constexpr uint32_t kErrDegree = 2u;   // a vertex reached degree 256
 constexpr uint32_t kErrValue = 4u;    // a static-function value outside [0, sigma)
+constexpr uint32_t kErrRounds = 8u;   // more rounds than the start arrays hold
 
 // Device-side control block of one peeling run (lives in the workspace).
 struct Ctrl {
@@ -29,7 +30,15 @@ struct Ctrl {
     unsigned long long updates;  // deletes applied through update lists
     unsigned long long touched;  // records those deletes changed
     unsigned long long dups;     // pairs of 2-core edges with equal vertex triples (failure path)
-    uint64_t pad[23];
+    // a run whose rounds share launches (rounds.hip)
+    unsigned long long f0;       // vertices of degree 1 before round 0
+    unsigned long long layer0;   // edges of layer 0
+    unsigned long long peeled;   // edges removed, once the peel has ended
+    unsigned long long run_lo;   // where the next launch goes on: start of layer run_r,
+    unsigned long long run_list; // its edges in the shared list,
+    uint32_t run_r;              // and the round
+    uint32_t pad32;
+    uint64_t pad[17];
 };
 static_assert(sizeof(Ctrl) == 256, "Ctrl is one 256-byte slot");
 

@@ -43,6 +43,7 @@ struct PeelState {
     const uint32_t* vin;
     uint32_t* vout;
     void* aux;              // partition histograms and scan scratch (part_aux_bytes)
+    struct GridSync* sync;  // two groups' barrier state (rounds.hip)
 };
 
 // utilities (scan.hip)
@@ -120,6 +121,27 @@ hipError_t launch_close_layer(const PeelState& st, uint32_t r, hipStream_t s);
 enum class ApplyMode { kAtomicClaims, kClaimList, kUpdateList };
 // hinge_in_slot: layer r came from a resolved claim list
 hipError_t launch_apply(const PeelState& st, uint32_t r, bool hinge_in_slot, ApplyMode mode, hipStream_t s);
+// Runs of at most kRunMaxEdges edges (rounds.hip) peel in one launch: launch_run_init takes the
+// place of launch_ctrl_init; launch_round0 fills layer 0; launch_rounds peels until a layer is
+// empty (ctrl->nrounds, ctrl->peeled) or a launch's round limit is reached (nrounds still
+// 0xFFFFFFFF: launch_rounds_again, then launch_rounds again).  generic_shift: edge states of
+// launch_*_r, (round << 3) | position.  Above, a launch per round is as fast or faster: apply
+// launches against one launch took 2450 and 1832 us at 10^7 keys, 5760 and 5743 at 3x10^7, 11574
+// and 14285 at 6x10^7, where the rounds are bound by the device atomics and many small
+// workgroups keep more of them in flight.
+constexpr uint64_t kRunMaxEdges = 1ull << 24;  // (27-bit counts in a barrier's payload)
+size_t run_sync_bytes();
+hipError_t launch_run_init(const PeelState& st, hipStream_t s);
+hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, hipStream_t s);
+hipError_t launch_rounds_again(const PeelState& st, hipStream_t s);
+// All layers of a complete peel of nrounds rounds in one launch, any size; the MPHF's codes and
+// rank samples, or a static function's values u (over the records).  nrounds 0: enqueued behind
+// launch_rounds before its outcome is known, does nothing after an incomplete peel.
+// st.sync[1] is zeroed: by launch_run_init, else by launch_sync_zero.
+hipError_t launch_sync_zero(const PeelState& st, hipStream_t s);
+hipError_t launch_mphf_finish(const PeelState& st, uint32_t nrounds, uint64_t* codes, uint64_t* rank, uint32_t* bcount,
+                              hipStream_t s);
+hipError_t launch_sf_solve(const PeelState& st, uint32_t nrounds, uint64_t sigma, uint32_t b, hipStream_t s);
 hipError_t launch_peel_finalize(const uint32_t* state, uint64_t n, uint32_t* round, uint8_t* core_mask,
                                 uint8_t* hinge, hipStream_t s);
 uint64_t sort_tiles(uint64_t n);

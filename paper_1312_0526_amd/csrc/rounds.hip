@@ -1,0 +1,564 @@
+// Peeling rounds and the layered assignment of a run, each in ONE launch.
+//
+// A peel at gamma 1.23 takes about 60 synchronous rounds and as many assignment layers, and below
+// some 10^7 keys a round's work is far smaller than what a launch costs: at 10^6 keys k_apply took
+// 10.3 us a round and k_assign_round 4.4, of which the memory operations of a plateau round
+// (about 5,000 edges) need under 1.  Here a group of workgroups (grid.h) stays on the device and
+// goes through the rounds with a barrier between them.
+//
+// What bounds a round is then its chain of dependent accesses: edge and state, the deletes, the
+// claim, the barrier.  So the next layer never leaves the compute unit that found it: each
+// workgroup keeps the edges it claimed first in a list of its own in LDS and deletes them itself
+// in the next round.  Claims beyond the list's size, and round 0's layer, go through a list in
+// device memory that all members share.  The order of a layer's slots is free (Section 4.2), and
+// the layers come out back to back as the other paths write them.
+#include "common.h"
+#include "grid.h"
+#include "launch.h"
+
+#include <algorithm>
+
+namespace mphx {
+
+constexpr uint32_t kRoundsBlock = 512;
+constexpr uint32_t kPrivate = 4096;          // edges of a workgroup's own list
+constexpr uint32_t kRoundsPerLaunch = 1024;  // a longer peel goes on in another launch
+
+__global__ __launch_bounds__(256) void k_run_init(Ctrl* ctrl, uint64_t* lstart, unsigned long long* lcount,
+                                                  GridSync* sync, uint32_t nsync)
+{
+    unsigned long long* w = reinterpret_cast<unsigned long long*>(sync);
+    for (uint32_t i = threadIdx.x; i < nsync * (sizeof(GridSync) / 8); i += 256)
+        w[i] = 0;
+    if (threadIdx.x < sizeof(Ctrl) / 8)
+        reinterpret_cast<uint64_t*>(ctrl)[threadIdx.x] = 0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        ctrl->nrounds = 0xFFFFFFFFu;
+        lstart[0] = 0;
+        lcount[0] = 0;
+    }
+}
+
+// Lane of the active ones appends one entry: one LDS atomic per wave.
+__device__ __forceinline__ uint32_t lds_append(uint32_t* counter)
+{
+    const uint64_t mask = __ballot(1);
+    const int leader = __ffsll((long long)mask) - 1;
+    uint32_t base = 0;
+    if ((int)__lane_id() == leader)
+        base = atomicAdd(counter, (uint32_t)__popcll(mask));
+    return (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + lanes_below(mask);
+}
+
+// A range shared by the members is dealt out wave by wave, so that a range shorter than the group
+// still occupies as many compute units as it has waves: a layer of 3,300 edges dealt out by
+// workgroups of 1024 kept four compute units busy for 4.6 us.
+__device__ __forceinline__ uint64_t member_first(const Grid& g)
+{
+    const uint32_t wave = threadIdx.x / kWave;
+    return ((uint64_t)wave * g.members + g.rank) * kWave + (threadIdx.x & (kWave - 1));
+}
+__device__ __forceinline__ uint64_t member_stride(const Grid& g) { return (uint64_t)g.members * kRoundsBlock; }
+
+struct RoundsArgs {
+    uint64_t* rec;
+    const uint32_t* edges;
+    uint32_t* state;
+    uint3* slots;
+    uint64_t* lstart;
+    const unsigned long long* lcount;
+    Ctrl* ctrl;
+    GridSync* sync;
+    uint64_t n, P, rcap;
+    const uint32_t* vin;  // static functions: see PeelState
+    uint32_t* vout;
+};
+
+// Edges of kR vertices; an edge state is unclaimed or (round << kShift) | hinge position; with
+// kTri the vertex of position q lies in part q and the layer slots are rewritten hinge first.
+// The edge of layer r is deleted at its vertices other than the hinge; the delete that takes a
+// vertex from degree 2 to 1 claims the vertex's last edge for round r + 1 (lowest position wins)
+// and its first claimer appends the edge, as in k_apply.
+template <int kR, bool kTri, int kShift>
+__global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
+{
+    static_assert(!kTri || kR == 3, "parts hold one vertex each");
+    __shared__ uint32_t s_list[2][kPrivate];
+    __shared__ uint32_t s_next[2], s_join[2];
+    __shared__ uint64_t s_total, s_off;
+    __shared__ unsigned long long s_push, s_claims;
+    Grid g;
+    if (!grid_join(a.sync, g, s_join))
+        return;
+    const uint32_t tid = threadIdx.x;
+    const bool lead = g.rank == 0 && tid == 0;
+    Ctrl* const c = a.ctrl;
+    uint64_t lo = c->run_lo, glist = c->run_list;
+    uint32_t r = c->run_r;
+    if (r == 0) {
+        // a degree above 255 (see k_round0) or a bad edge: nothing may be read off the records
+        if ((c->err & (kErrDegree | kErrBadEdge)) || c->degsum != (uint64_t)kR * a.n)
+            return;
+        glist = a.lcount[0];
+        if (lead) {
+            c->f0 = c->ftail;  // before any member adds to it
+            c->layer0 = glist;
+        }
+    }
+    unsigned long long* const pcur = &a.sync->cursor[0].w;  // edges of private lists, all rounds
+    unsigned long long* const gcur = &a.sync->cursor[1].w;  // edges of shared lists, all rounds
+    uint64_t psum = 0, gsum = 0;  // what the cursors passed before this round
+    uint64_t ptot = 0;            // this layer's private edges
+    uint32_t pc = 0, cur = 0, done = 0;
+    uint64_t pbase = 0;
+    unsigned long long mypush = 0, myclaims = 0;
+    // this thread's first private edge and its vertices, loaded while the group waited
+    uint32_t e0 = 0, v0[kR] = {};
+    if (tid == 0) {
+        s_next[0] = s_next[1] = 0;
+        s_push = s_claims = 0;
+    }
+    __syncthreads();
+    bool more = false;
+    for (;; r++, done++) {
+        if (lead && r < a.rcap + 2)
+            a.lstart[r] = lo;
+        if (r >= a.rcap) {
+            if (lead)
+                atomicOr(&c->err, kErrRounds);
+            break;
+        }
+        // layer r: slots [lo, lo + glist) hold the shared list's edges, the private lists follow
+        const uint64_t hi = lo + glist + ptot;
+        if (lo == hi)
+            break;
+        if (done == kRoundsPerLaunch) {
+            more = true;
+            break;
+        }
+        // the last round of a launch leaves the next layer in the shared list
+        const uint32_t cap = done + 1 == kRoundsPerLaunch ? 0u : kPrivate;
+        const uint32_t rr = (r + 1) << kShift;
+        uint32_t* const next = s_list[cur ^ 1];
+        uint32_t* const count = &s_next[cur ^ 1];
+        auto append = [&](uint32_t e) {
+            const uint32_t pos = lds_append(count);
+            if (pos < cap) {
+                next[pos] = e;
+            } else {
+                const uint64_t idx = wave_append(gcur, true, false) - gsum;
+                ag_store(&a.slots[hi + idx].x, e);
+            }
+        };
+        // old[q]: record of vertex v[q] before e's delete (0 where e was not deleted).  All claims
+        // are in flight before the first is looked at.
+        auto claim = [&](uint32_t e, const uint32_t (&v)[kR], const uint64_t (&old)[kR]) {
+            uint32_t x[kR], o[kR];
+#pragma unroll
+            for (uint32_t q = 0; q < kR; q++) {
+                if (Rec::deg(old[q]) == 2) {
+                    x[q] = (uint32_t)(Rec::edge(old[q]) - e);
+                    uint32_t p = q;
+                    if constexpr (!kTri) {
+                        const uint32_t* t = a.edges + (uint64_t)kR * x[q];
+                        p = 0;
+#pragma unroll
+                        for (uint32_t k = 1; k < kR; k++)
+                            if (t[k] == v[q])
+                                p = k;
+                    }
+                    o[q] = __hip_atomic_fetch_min(&a.state[x[q]], rr | p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < kR; q++) {
+                if (Rec::deg(old[q]) == 2) {
+                    const bool first = o[q] == kUnclaimed;
+                    mypush++;
+                    myclaims += (first || (o[q] >> kShift) == r + 1) ? 1u : 0u;
+                    if (first)
+                        append(x[q]);
+                }
+            }
+        };
+        auto hinge_first = [&](uint32_t h, const uint32_t (&v)[kR]) {
+            return make_uint3(h == 0 ? v[0] : (h == 1 ? v[1] : v[kR - 1]), h == 0 ? v[1] : (h == 1 ? v[kR - 1] : v[0]),
+                              h == 0 ? v[kR - 1] : (h == 1 ? v[0] : v[1]));
+        };
+        // an edge of a long list: the hinge is read first and saves its delete
+        auto peel = [&](uint32_t e, uint64_t pos) {
+            const uint32_t h = ag_load(&a.state[e]) & ((1u << kShift) - 1);
+            const uint32_t* t = a.edges + (uint64_t)kR * e;
+            uint32_t v[kR];
+            uint64_t old[kR];
+#pragma unroll
+            for (uint32_t q = 0; q < kR; q++)
+                v[q] = t[q];
+#pragma unroll
+            for (uint32_t q = 0; q < kR; q++)
+                old[q] = q != h ? ag_add(a.rec + v[q], 0ull - (Rec::kOne + e)) : 0ull;
+            if constexpr (kTri) {
+                a.slots[pos] = hinge_first(h, v);
+                if (a.vin)
+                    a.vout[pos] = a.vin[e];
+            }
+            claim(e, v, old);
+        };
+        // a thread's first private edge: the deletes do not wait for the state -- the hinge's
+        // record, of degree 1, drops to 0 -- and the slot is written after the group is told
+        uint3 slot = make_uint3(0u, 0u, 0u);
+        const bool mine = tid < pc;
+        const uint32_t e1 = e0;
+        if (mine) {
+            uint64_t old[kR];
+#pragma unroll
+            for (uint32_t q = 0; q < kR; q++)
+                old[q] = ag_add(a.rec + v0[q], 0ull - (Rec::kOne + e1));
+            if constexpr (kTri)
+                slot = hinge_first(ag_load(&a.state[e1]) & ((1u << kShift) - 1), v0);
+            claim(e1, v0, old);
+        }
+        for (uint32_t i = tid + kRoundsBlock; i < pc; i += kRoundsBlock)
+            peel(s_list[cur][i], pbase + i);
+        for (uint64_t j = member_first(g); j < glist; j += member_stride(g))
+            peel(ag_load(&a.slots[lo + j].x), lo + j);
+        uint32_t pnext = 0;
+        const uint64_t total = grid_barrier(
+            g, &s_total,
+            [&]() -> uint64_t {
+                const uint32_t k = *count, p = min(k, cap);
+                s_next[cur] = 0;
+                // where this workgroup's private edges of the next layer go, asked for ahead
+                s_off = p ? ag_add(pcur, p) : 0ull;
+                return (uint64_t)p | (uint64_t)(k - p) << 27;
+            },
+            [&] {
+                if constexpr (kTri) {
+                    if (mine) {
+                        a.slots[pbase + tid] = slot;
+                        if (a.vin)
+                            a.vout[pbase + tid] = a.vin[e1];
+                    }
+                }
+                pnext = min(*count, cap);
+                if (tid < pnext) {
+                    e0 = next[tid];
+#pragma unroll
+                    for (uint32_t q = 0; q < kR; q++)
+                        v0[q] = a.edges[(uint64_t)kR * e0 + q];
+                }
+            });
+        lo = hi;
+        ptot = total & ((1ull << 27) - 1);
+        glist = total >> 27;
+        pc = pnext;
+        pbase = lo + glist + (s_off - psum);
+        psum += ptot;
+        gsum += glist;
+        cur ^= 1;
+    }
+    if (lead) {
+        if (more) {
+            c->run_lo = lo;
+            c->run_list = glist;
+            c->run_r = r;
+        } else if (r < a.rcap) {
+            c->nrounds = r;
+            c->peeled = lo;
+        }
+    }
+    if (mypush) atomicAdd(&s_push, mypush);
+    if (myclaims) atomicAdd(&s_claims, myclaims);
+    __syncthreads();
+    if (tid == 0) {
+        if (s_push) atomicAdd(&c->ftail, s_push);
+        if (s_claims) atomicAdd(&c->claims, s_claims);
+    }
+}
+
+// The layers of a complete peel, last first, with a barrier after each: load(i) reads slot i, which
+// nobody changes, and solve(item) solves it; a thread's first slot of the next layer is read while
+// the group waits.  The layers at the end of a peel hold few edges: member 0 alone goes through
+// those at the top that one pass of its threads covers, with barriers of its own.
+constexpr uint32_t kLayerChunk = 1024;
+template <class Item, class Load, class Solve>
+__device__ __forceinline__ void solve_layers(Grid& g, const uint64_t* __restrict__ lstart, uint32_t nrounds,
+                                             uint64_t* s_ls, uint64_t* s_total, Load load, Solve solve)
+{
+    const uint32_t tid = threadIdx.x;
+    const uint64_t first = member_first(g), stride = member_stride(g);
+    bool solo = true, have = false;
+    Item ahead{};
+    uint32_t top = nrounds;  // layers [base, top) have their bounds in s_ls
+    while (top > 0) {
+        const uint32_t base = top > kLayerChunk ? top - kLayerChunk : 0;
+        __syncthreads();
+        for (uint32_t k = tid; k <= top - base; k += kRoundsBlock)
+            s_ls[k] = lstart[base + k];
+        __syncthreads();
+        for (uint32_t k = top - base; k-- > 0;) {
+            const uint64_t lo = s_ls[k], hi = s_ls[k + 1];
+            const uint64_t below = k ? s_ls[k - 1] : lo;  // the next layer is [below, lo)
+            if (solo && hi - lo <= kRoundsBlock) {
+                if (g.rank == 0) {
+                    if (lo + tid < hi)
+                        solve(have ? ahead : load(lo + tid));
+                    have = k && lo - below <= kRoundsBlock;
+                    if (have && below + tid < lo)
+                        ahead = load(below + tid);
+                    drain_memory();
+                    __syncthreads();
+                }
+                continue;
+            }
+            if (solo) {
+                solo = have = false;
+                grid_barrier(g, s_total);
+            }
+            uint64_t i = lo + first;
+            if (i < hi) {
+                solve(have ? ahead : load(i));
+                for (i += stride; i < hi; i += stride)
+                    solve(load(i));
+            }
+            have = k != 0;
+            grid_barrier(
+                g, s_total, []() -> uint64_t { return 0; },
+                [&] {
+                    if (have && below + first < lo)
+                        ahead = load(below + first);
+                });
+        }
+        top = base;
+    }
+    if (solo)
+        grid_barrier(g, s_total);
+}
+
+__device__ __forceinline__ void zero_shared(Grid& g, uint64_t* p, uint64_t words)
+{
+    for (uint64_t i = member_first(g); i < words; i += member_stride(g))
+        ag_store(p + i, (uint64_t)0);
+}
+
+// The whole rest of an MPHF build whose peel is complete: the codes (one byte per vertex, over
+// the records), layer by layer; the packed codes and rank samples, each member's share of the
+// vertices after a prefix over the members.  Does nothing after an incomplete peel.
+__global__ __launch_bounds__(kRoundsBlock) void k_mphf_finish(const uint3* __restrict__ slots,
+                                                              const uint64_t* __restrict__ lstart, const Ctrl* ctrl,
+                                                              GridSync* sync, uint32_t nrounds, uint64_t n, uint64_t m,
+                                                              uint64_t P, uint64_t* code_words, uint64_t* __restrict__ codes,
+                                                              uint64_t* __restrict__ rank, uint32_t* bcount)
+{
+    __shared__ uint32_t s_join[2];
+    __shared__ uint64_t s_total, s_ls[kLayerChunk + 1], s_wave[kRoundsBlock / kWave], s_carry;
+    if (nrounds == 0) {  // enqueued behind launch_rounds
+        nrounds = ctrl->nrounds;
+        if (nrounds == 0xFFFFFFFFu || ctrl->peeled != n)
+            return;
+    }
+    Grid g;
+    if (!grid_join(sync, g, s_join))
+        return;
+    uint8_t* const code8 = reinterpret_cast<uint8_t*>(code_words);
+    zero_shared(g, code_words, (m + 7) / 8);  // 8m bytes of records hold it
+    grid_barrier(g, &s_total);
+    solve_layers<uint3>(g, lstart, nrounds, s_ls, &s_total, [&](uint64_t i) { return slots[i]; }, [&](uint3 t) {
+        const uint32_t k = part_of(t.x, P);
+        const uint32_t ca = ag_load(code8 + t.y), cb = ag_load(code8 + t.z);
+        const uint32_t x = (k + 6 - (ca == 3 ? 0u : ca) - (cb == 3 ? 0u : cb)) % 3;
+        ag_store(code8 + t.x, (uint8_t)(x ? x : 3));
+    });
+    // this member's rank blocks [b0, b1) of 512 vertices, one thread per code word of 32
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const uint64_t nwords = (m + 31) / 32, nb = (m + 511) / 512, per = (nb + g.members - 1) / g.members;
+    const uint64_t b0 = min(nb, g.rank * per), b1 = min(nb, b0 + per);
+    uint64_t mine = 0;
+    for (uint64_t base = 16 * b0; base < 16 * b1; base += kRoundsBlock) {
+        const uint64_t w = base + tid;
+        uint64_t x = 0;
+        if (w < 16 * b1 && w < nwords) {
+            if (32 * w + 32 <= m) {
+#pragma unroll
+                for (uint32_t q = 0; q < 4; q++) {
+                    const uint64_t d = ag_load(code_words + 4 * w + q);
+#pragma unroll
+                    for (uint32_t t = 0; t < 8; t++)
+                        x |= (d >> (8 * t) & 3u) << (2 * (8 * q + t));
+                }
+            } else {
+                for (uint64_t t = 0; 32 * w + t < m; t++)
+                    x |= (uint64_t)(ag_load(code8 + 32 * w + t) & 3u) << (2 * t);
+            }
+            codes[w] = x;
+        }
+        uint32_t k = nz_pairs(x);
+        k += __shfl_xor(k, 1, 16);
+        k += __shfl_xor(k, 2, 16);
+        k += __shfl_xor(k, 4, 16);
+        k += __shfl_xor(k, 8, 16);
+        if (w < 16 * b1 && (w & 15) == 0) {
+            bcount[w >> 4] = k;  // read by this workgroup only
+            mine += k;
+        }
+    }
+    for (uint32_t d = kWave / 2; d > 0; d >>= 1)
+        mine += __shfl_xor(mine, d, kWave);
+    if (lane == 0)
+        s_wave[wv] = mine;
+    __syncthreads();
+    if (tid == 0) {
+        uint64_t t = 0;
+        for (uint32_t q = 0; q < kRoundsBlock / kWave; q++)
+            t += s_wave[q];
+        ag_store(&sync->sums[g.rank], (unsigned long long)t);
+        s_carry = 0;
+    }
+    grid_barrier(g, &s_total);
+    if (wv == 0) {  // hinges below this member's first vertex
+        uint64_t t = 0;
+        for (uint32_t q = lane; q < g.rank; q += kWave)
+            t += ag_load(&sync->sums[q]);
+        for (uint32_t d = kWave / 2; d > 0; d >>= 1)
+            t += __shfl_xor(t, d, kWave);
+        if (lane == 0)
+            s_carry = t;
+    }
+    __syncthreads();
+    for (uint64_t base = b0; base < b1; base += kRoundsBlock) {
+        const uint64_t b = base + tid;
+        const uint64_t x = b < b1 ? bcount[b] : 0u;
+        uint64_t incl = x;
+        for (uint32_t d = 1; d < kWave; d <<= 1) {
+            const uint64_t y = __shfl_up(incl, d, kWave);
+            if (lane >= d)
+                incl += y;
+        }
+        if (lane == kWave - 1)
+            s_wave[wv] = incl;
+        __syncthreads();
+        uint64_t pre = s_carry;
+        for (uint32_t q = 0; q < wv; q++)
+            pre += s_wave[q];
+        if (b < b1)
+            rank[b] = pre + incl - x;
+        __syncthreads();
+        if (tid == kRoundsBlock - 1)
+            s_carry = pre + incl;
+        __syncthreads();
+    }
+}
+
+// The values u of a static function whose peel is complete (zero off the hinges), as
+// k_sf_assign_round solves them.  Does nothing after an incomplete peel.
+template <typename T>
+__global__ __launch_bounds__(kRoundsBlock) void k_sf_solve(const uint3* __restrict__ slots,
+                                                           const uint32_t* __restrict__ vals,
+                                                           const uint64_t* __restrict__ lstart, const Ctrl* ctrl,
+                                                           GridSync* sync, uint32_t nrounds, uint64_t n, uint64_t m,
+                                                           uint64_t sigma, uint64_t* u_words)
+{
+    __shared__ uint32_t s_join[2];
+    __shared__ uint64_t s_total, s_ls[kLayerChunk + 1];
+    if (nrounds == 0) {  // enqueued behind launch_rounds
+        nrounds = ctrl->nrounds;
+        if (nrounds == 0xFFFFFFFFu || ctrl->peeled != n)
+            return;
+    }
+    Grid g;
+    if (!grid_join(sync, g, s_join))
+        return;
+    T* const u = reinterpret_cast<T*>(u_words);
+    zero_shared(g, u_words, (m * sizeof(T) + 7) / 8);
+    grid_barrier(g, &s_total);
+    auto load = [&](uint64_t i) { return make_uint4(slots[i].x, slots[i].y, slots[i].z, vals[i]); };
+    solve_layers<uint4>(g, lstart, nrounds, s_ls, &s_total, load, [&](uint4 t) {
+        uint64_t x = (uint64_t)t.w + 2 * sigma - ag_load(u + t.y) - ag_load(u + t.z);
+        x = x >= sigma ? x - sigma : x;
+        x = x >= sigma ? x - sigma : x;
+        ag_store(u + t.x, (T)x);
+    });
+}
+
+// ------------------------------------------------------------------------------------------
+size_t run_sync_bytes() { return 2 * sizeof(GridSync); }
+
+// Members of a group for n edges.  Few make the barrier cheap (0.8 us at 8 members, 1.3 at 64), many
+// hide the latency of the large first rounds; whole builds of u64 keys took, in us:
+//   members            8     16     32     64    128    192    256
+//   10^5 keys        614    535    522    560    573    592    608
+//   3x10^5          1080    832    730    754    769    807    829
+//   10^6            2441   1529   1112    980    954   1001   1044
+//   3x10^6          6307   3550   2344   1787   1532   1551   1597
+//   10^7           22579  11894   7325   5286   3965   3565   3374
+static unsigned run_grid(const PeelState& st)
+{
+    const uint64_t n = st.n;
+    uint64_t g = std::max({std::min<uint64_t>(n / 4096, 32), std::min<uint64_t>(n / 8192, 128), n / 40960});
+    if (st.grid_cap) g = st.grid_cap;
+    return (unsigned)std::min<uint64_t>(std::max<uint64_t>(g, 1), kGridMax);
+}
+
+hipError_t launch_run_init(const PeelState& st, hipStream_t s)
+{
+    k_run_init<<<1, 256, 0, s>>>(st.ctrl, st.lstart, st.lcount, st.sync, 2);
+    return hipGetLastError();
+}
+
+hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, hipStream_t s)
+{
+    if (st.n > kRunMaxEdges) return hipErrorInvalidValue;
+    const RoundsArgs a{st.rec, st.edges, st.state, st.slots, st.lstart, st.lcount, st.ctrl, st.sync,
+                       st.n,   st.P,     st.rcap,  st.vin,   st.vout};
+    const unsigned g = run_grid(st);
+    if (st.tripartite) {
+        if (r != 3 || generic_shift) return hipErrorInvalidValue;
+        k_rounds<3, true, 2><<<g, kRoundsBlock, 0, s>>>(a);
+        return hipGetLastError();
+    }
+    if (!generic_shift) {
+        if (r != 3) return hipErrorInvalidValue;
+        k_rounds<3, false, 2><<<g, kRoundsBlock, 0, s>>>(a);
+        return hipGetLastError();
+    }
+    switch (r) {
+    case 2: k_rounds<2, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 3: k_rounds<3, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 4: k_rounds<4, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 5: k_rounds<5, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 6: k_rounds<6, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 7: k_rounds<7, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 8: k_rounds<8, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_sync_zero(const PeelState& st, hipStream_t s) { return launch_zero(st.sync, run_sync_bytes(), s); }
+hipError_t launch_rounds_again(const PeelState& st, hipStream_t s) { return launch_sync_zero(st, s); }
+
+hipError_t launch_mphf_finish(const PeelState& st, uint32_t nrounds, uint64_t* codes, uint64_t* rank, uint32_t* bcount,
+                              hipStream_t s)
+{
+    k_mphf_finish<<<run_grid(st), kRoundsBlock, 0, s>>>(st.slots, st.lstart, st.ctrl, st.sync + 1, nrounds, st.n, st.m,
+                                                        st.P, st.rec, codes, rank, bcount);
+    return hipGetLastError();
+}
+
+hipError_t launch_sf_solve(const PeelState& st, uint32_t nrounds, uint64_t sigma, uint32_t b, hipStream_t s)
+{
+    const unsigned g = run_grid(st);
+#define MPHX_SOLVE(T) \
+    k_sf_solve<T><<<g, kRoundsBlock, 0, s>>>(st.slots, st.vout, st.lstart, st.ctrl, st.sync + 1, nrounds, st.n, st.m, \
+                                            sigma, st.rec)
+    switch (sf_elem_bytes(b)) {
+    case 1: MPHX_SOLVE(uint8_t); break;
+    case 2: MPHX_SOLVE(uint16_t); break;
+    default: MPHX_SOLVE(uint32_t);
+    }
+#undef MPHX_SOLVE
+    return hipGetLastError();
+}
+
+}  // namespace mphx
