@@ -614,10 +614,11 @@ MPHX_API int mphx_gen_str_bytes(uint8_t* bytes, const uint64_t* offs, uint64_t n
  *                 claims of the next round then come from the updated records.  0 = never.
  *                 The same codes either way.
  *   "batch_lds"   1 (default) = in the batched kernel (mphx_build_batch*, the server's
- *                 batching lane, the HEM split) a bucket whose 4-byte records and edge states
- *                 fit in the workgroup's LDS budget (1024 threads: 158 KB, about 18,000 keys;
- *                 512: 78 KB, about 9,000; 256: 48 KB, about 5,500) is built and peeled
- *                 entirely in LDS; 0 = every bucket through device memory.
+ *                 batching lane, the HEM split) a bucket whose graph fits in the workgroup's LDS
+ *                 budget at 7 bytes per vertex (1024 threads: 158 KB, about 18,500 keys; 512: 78
+ *                 KB, about 9,000; 256: 48 KB, about 5,400) is built entirely in LDS.  A launch
+ *                 whose largest bucket fits in 158 KB consists of such builds alone, several per
+ *                 compute unit when their LDS allows.  0 = every bucket through device memory.
  *                 The same codes either way.
  *   "batch_sort_deletes" d in 0..1024 (default 4): in the batched kernel, a layer of a
  *                 bucket given by key words (at most 2^20 keys, built through device memory)

@@ -239,8 +239,66 @@ void layout_mphf(Carve& c, uint64_t n, uint64_t m, bool lists, MphfLayout& L, bo
 
 bool aligned256(const void* p) { return ((uintptr_t)p & 255) == 0; }
 
+// Pinned words that kernels report through: writing one costs a build less than a copy back does
+// (about 10 us at 10^3 keys).  64 slots, taken for the time of a read and given back; with none
+// left, or no pinned memory, the caller copies instead.
+class HostSlot {
+    static constexpr int kSlots = 64;
+    struct Pool {
+        std::mutex mu;
+        uint64_t used = 0;
+        uint8_t* base = nullptr;
+        bool tried = false;
+    };
+    static Pool& pool()
+    {
+        static Pool* p = new Pool;  // never freed: threads may still read at exit
+        return *p;
+    }
+    int i_ = -1;
+
+public:
+    static constexpr size_t kBytes = 256;
+    HostSlot()
+    {
+        Pool& p = pool();
+        std::lock_guard<std::mutex> lk(p.mu);
+        if (!p.tried) {
+            p.tried = true;
+            void* q = nullptr;
+            if (hipHostMalloc(&q, kSlots * kBytes, hipHostMallocPortable) == hipSuccess)
+                p.base = (uint8_t*)q;
+            else
+                (void)hipGetLastError();
+        }
+        if (!p.base || !~p.used) return;
+        i_ = __builtin_ctzll(~p.used);
+        p.used |= 1ull << i_;
+    }
+    ~HostSlot()
+    {
+        if (i_ < 0) return;
+        Pool& p = pool();
+        std::lock_guard<std::mutex> lk(p.mu);
+        p.used &= ~(1ull << i_);
+    }
+    HostSlot(const HostSlot&) = delete;
+    HostSlot& operator=(const HostSlot&) = delete;
+    void* get() const { return i_ < 0 ? nullptr : pool().base + (size_t)i_ * kBytes; }
+};
+static_assert(sizeof(Ctrl) <= HostSlot::kBytes && sizeof(LdsOutcome) <= HostSlot::kBytes, "a slot holds a report");
+
 int read_ctrl(Ctrl* dctrl, Ctrl& h, hipStream_t s)
 {
+    HostSlot slot;
+    if (slot.get()) {
+        // the slot goes back only once the stream has passed the kernel that writes it
+        HIP_TRY(launch_copy_ctrl(dctrl, (Ctrl*)slot.get(), s));
+        const hipError_t e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return fail(MPHX_EDEVICE, "hipStreamSynchronize failed: %s", hipGetErrorString(e));
+        memcpy(&h, slot.get(), sizeof h);
+        return MPHX_OK;
+    }
     HIP_TRY(hipMemcpyAsync(&h, dctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     return MPHX_OK;
@@ -852,6 +910,67 @@ struct SfArgs {
     uint64_t* vals = nullptr;
 };
 
+// String keys beyond this many are hashed by a launch of their own, whose workgroups share them;
+// one workgroup hashes fewer at once.
+constexpr uint64_t kSmallStrHash = 2048;
+constexpr uint32_t kFirstTryAgain = 0xFFFFFFFFu;
+
+// The whole build in one workgroup.  first is 0 when it is done; else the general path has to make
+// the tries from there on: the last one, which left a 2-core whose edges it looks at, or one with
+// a degree above 255, which it reports.
+int small_build(const KeySrc& k, uint64_t n, uint64_t seed, uint64_t P, uint32_t max_tries, uint64_t* codes,
+                uint64_t* rank, const MphfLayout& L, hipStream_t s, mphx_mphf_info* info, uint32_t& first)
+{
+    SmallArgs a{};
+    if (k.kind == MPHX_KEYS_U64) {
+        a.keys = k.keys;
+    } else {
+        a.bytes = k.bytes;
+        a.offs = k.offs;
+        if (n > kSmallStrHash) {
+            Timed tm(PH_HASH, s);
+            HIP_TRY(launch_hash_str(k.bytes, k.offs, n, seed, P, L.edges, nullptr, PartHist1{nullptr, 0, 0}, s));
+            a.edges = L.edges;
+        }
+    }
+    a.n = (uint32_t)n;
+    a.P = (uint32_t)P;
+    a.seed = seed;
+    a.max_tries = max_tries;
+    a.queue = reinterpret_cast<uint16_t*>(L.rec);
+    a.start = reinterpret_cast<uint32_t*>(L.lstart);
+    a.codes = codes;
+    a.rank = rank;
+    HostSlot slot;
+    a.out = slot.get() ? (LdsOutcome*)slot.get() : (LdsOutcome*)L.ctrl;
+    {
+        Timed tm(PH_APPLY, s);
+        HIP_TRY(launch_small_build(a, s));
+    }
+    LdsOutcome o{};
+    if (!slot.get()) HIP_TRY(hipMemcpyAsync(&o, L.ctrl, sizeof o, hipMemcpyDeviceToHost, s));
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail(MPHX_EDEVICE, "hipStreamSynchronize failed: %s", hipGetErrorString(e));
+    if (slot.get()) memcpy(&o, slot.get(), sizeof o);
+    g_timers.harvest();
+    if (o.status) {
+        first = o.tries - 1;
+        if (first == 0) first = kFirstTryAgain;
+        return MPHX_OK;
+    }
+    first = 0;
+    if (info) {
+        info->tries = o.tries;
+        info->seed_used = o.seed;
+        info->n_rounds = o.rounds;
+        info->frontier_total = o.frontier;
+        info->claims = o.claims;
+        info->frontier0 = o.frontier0;
+        info->layer0 = o.layer0;
+    }
+    return MPHX_OK;
+}
+
 // The values of every vertex take this much at most: all layers in one launch (launch_mphf_finish,
 // launch_sf_solve), else a launch per layer with non-temporal reads.  One launch keeps fewer
 // accesses in flight, which leaves more of a layer's values in the 256 MB memory-side cache; once
@@ -927,6 +1046,13 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
     Carve c(ws);
     MphfLayout L;
     layout_mphf(c, n, m, lists, L, sf != nullptr);
+    uint32_t t0 = 0;  // the first try that is left to do
+    const bool part = g_opt.part_build.load() > 0 && n >= (1ull << g_opt.part_build.load());  // part_build <= 32
+    if (!sf && !lists && !part && g_opt.grid.load() == 0 && small_build_fits(n, m)) {
+        int rc = small_build(k, n, seed, P, max_tries, codes, rank, L, s, info, t0);
+        if (rc || t0 == 0) return rc;
+        if (t0 == kFirstTryAgain) t0 = 0;
+    }
     if (sf) {  // every value below sigma
         HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
         HIP_TRY(launch_sf_check(sf->values, n, sf->sigma, L.ctrl, s));
@@ -969,10 +1095,8 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
         return sf ? launch_sf_solve(st, nrounds, sf->sigma, mphx_sf_bits(sf->sigma), s)
                   : launch_mphf_finish(st, nrounds, codes, rank, L.bcount, s);
     };
-    for (t = 0; t < max_tries; t++) {
+    for (t = t0; t < max_tries; t++) {
         uint64_t sd = seed + t;
-        const int pb = g_opt.part_build.load();
-        const bool part = pb > 0 && n >= (1ull << pb);  // pb <= 32
         if (!part)
             HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
         grid_run = !st.lists && n <= kRunMaxEdges;

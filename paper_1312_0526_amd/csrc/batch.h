@@ -31,13 +31,16 @@ struct BatchArgs {
     uint8_t* slots;
     uint64_t slot_bytes;
     uint64_t max_n;          // largest bucket a slot can hold
-    unsigned int* next;      // queue cursor
+    unsigned int* next;      // queue cursors: [0] buckets through device memory, [1] in LDS, [3] those
+                             // left to a second launch; [2] how many these are
     uint32_t lds_path;       // 1: buckets that fit run in LDS
     uint32_t sort_div;       // > 0: a layer deletes through a sorted list when 2 * layer * sort_div >= m
     uint32_t pairs;          // 1: every bucket's keys are 128-bit digest pairs (2 u64 words per key:
                              // the edge under seed t is that of the digest (x ^ t, y ^ t))
     uint32_t claim_lists;    // 1: sparse rounds of buckets given by key words resolve their claims
                              // through a list grouped by edge tile, in LDS, instead of atomicMin
+    uint32_t lds_bytes;      // LDS that a bucket built there may take
+    uint32_t left_only;      // 1: the second launch, for the buckets that the first has marked
     uint32_t clock;          // 1: launch the kernel that adds its per-phase workgroup time and
                              // work counts to the device's batch clock
 };

@@ -19,6 +19,9 @@
 #include "common.h"
 #include "batch.h"
 #include "launch.h"
+#include "lds_build.h"
+
+#include <algorithm>
 
 namespace mphx {
 
@@ -192,9 +195,9 @@ __device__ uint32_t lds_exclusive_scan(uint32_t* a, uint32_t count, uint32_t* wt
 template <int kBlock>
 constexpr uint32_t batch_tile() { return kBlock >= 1024 ? 8192u : 4096u; }
 constexpr uint32_t kBatchMaxBuckets = 2048;
-// LDS shared by the two bucket builds: the partitioned record build's tile, counts and bounds,
-// or a whole bucket's 4-byte records and edge states.  1024-thread workgroups take 158 KB (one
-// per compute unit), 512-thread ones 78 KB (two), 256-thread ones 48 KB (three).
+// LDS of the partitioned record build's tile, counts and bounds, or a whole bucket's graph: 1024-thread
+// workgroups take 158 KB (one per compute unit), 512-thread ones 78 KB (two), 256-thread ones 48 KB
+// (three).
 template <int kBlock>
 constexpr uint32_t batch_part_bytes() { return batch_tile<kBlock>() * 8 + (2 * kBatchMaxBuckets + 1) * 4; }
 template <int kBlock>
@@ -202,12 +205,14 @@ constexpr uint32_t batch_lds_bytes()
 {
     return kBlock >= 1024 ? 158u * 1024 : (kBlock >= 512 ? 78u * 1024 : batch_part_bytes<kBlock>());
 }
-// A bucket whose records (m words) and states (n words) fit runs entirely in LDS.
-template <int kBlock>
-__device__ __forceinline__ bool bucket_fits_lds(uint64_t n, uint64_t m)
+// Whether a bucket's graph and queue fit in `bytes` of LDS (lds_build.h).
+__device__ __forceinline__ bool bucket_fits_lds(const BatchArgs& a, uint64_t n, uint32_t bytes)
 {
-    return ((m + 3) & ~3ull) + n <= batch_lds_bytes<kBlock>() / 4;
+    const uint64_t m = 3 * part_size_dev(n, a.gnum, a.gden);
+    return a.lds_path && n <= a.max_n && m <= kLdsMaxVertices && lds_build_bytes((uint32_t)m, true) <= bytes;
 }
+// Result status of a bucket whose degrees do not fit: a k_batch behind the launch builds it.
+constexpr int32_t kStatusLeft = 0x7FFFFFFF;
 
 // Digest of key i under seed sd for keys given by words: a u64 key x is the digest (x ^ sd,
 // x ^ sd), a digest pair (x, y) the digest (x ^ sd, y ^ sd).
@@ -268,7 +273,7 @@ __device__ __forceinline__ void write_result(BucketResult* r, uint64_t seed_used
     r->n_rounds = rounds;
 }
 
-// Codes (one byte per vertex, code8 in device memory or LDS) packed 2 bits per vertex into
+// Codes (one byte per vertex, code8) packed 2 bits per vertex into
 // d.codes, counted per 512 vertices and scanned into the rank samples d.rank.
 template <int kBlock>
 __device__ void pack_codes(const uint8_t* code8, uint32_t m, const BucketDesc& d, const SlotLayout& L)
@@ -1068,217 +1073,162 @@ __device__ void build_bucket(const BatchArgs& a, const BucketDesc& d, uint8_t* s
     clk.flush(n, t + 1, nrounds);
 }
 
-// The same build for a bucket that fits in LDS: 4-byte records (degree in bits [24, 32), sum of
-// incident edge ids in [0, 24): no carry while degrees stay <= 255 and ids below 2^16) and the
-// edge states live in LDS, so every atomic of the rounds is an LDS atomic; the layer slots stay
-// in the slot area.  Same rounds, hinges and layers as build_bucket, hence the same codes.
-template <int kBlock>
-__device__ void build_bucket_lds(const BatchArgs& a, const BucketDesc& d, uint8_t* slot, uint8_t* lds)
-{
-    __shared__ uint32_t s_ltail, s_err;
-    constexpr uint32_t kOne32 = 1u << 24, kSum = kOne32 - 1;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t n = (uint32_t)d.n;
-    const uint64_t P = part_size_dev(n, a.gnum, a.gden);
-    const uint32_t m = (uint32_t)(3 * P);
-    SlotLayout L;
-    slot_layout(slot, n, m, &L);
-    uint32_t* rec = reinterpret_cast<uint32_t*>(lds);  // m records
-    uint32_t* state = rec + ((m + 3) & ~3u);            // n edge states
-    const uint64_t total = d.keys ? 0 : d.offs[n];
-
-    uint32_t t = 0, nrounds = 0;
-    bool ok = false;
-    int status = 0;
-    uint64_t sd = d.seed;
-    for (t = 0; t < a.max_tries; t++) {
-        sd = d.seed + t;
-        for (uint32_t v = tid; v < m; v += kBlock)
-            rec[v] = 0;
-        for (uint32_t e = tid; e < n; e += kBlock)
-            state[e] = kUnclaimed;
-        if (tid == 0) {
-            s_ltail = 0;
-            s_err = 0;
-        }
-        const uint64_t sa = fin(sd + kGamma), sb = fin(sd + 2 * kGamma);
-        if (!d.keys) {  // string keys: digest once, keep the edges
-            for (uint32_t i = tid; i < n; i += kBlock) {
-                uint64_t o0 = d.offs[i], o1 = d.offs[i + 1], ha, hb;
-                digest_str(d.bytes, o0, o1 - o0, total, sa, sb, ha, hb);
-                uint3 ev;
-                edge_of_digest(ha, hb, P, ev.x, ev.y, ev.z);
-                L.edges[i] = ev;
-            }
-        }
-        __syncthreads();
-        for (uint32_t i = tid; i < n; i += kBlock) {
-            const uint3 ev = bucket_edge(a, d, L, i, sd, P);
-            const uint32_t o0 = atomicAdd(&rec[ev.x], kOne32 + i);
-            const uint32_t o1 = atomicAdd(&rec[ev.y], kOne32 + i);
-            const uint32_t o2 = atomicAdd(&rec[ev.z], kOne32 + i);
-            if (max(o0, max(o1, o2)) >= kMaxDegree * kOne32)  // a degree would pass 255
-                s_err = 1;
-        }
-        __syncthreads();
-        if (s_err) {
-            status = -2;  // degree above 255: no seed helps a duplicate-heavy bucket
-            break;
-        }
-        // round 0: a degree-1 vertex claims its edge; the lowest part wins
-        for (uint32_t base = 0; base < m; base += kBlock) {
-            const uint32_t v = base + tid;
-            bool first = false;
-            uint32_t e = 0;
-            if (v < m) {
-                const uint32_t x = rec[v];
-                if ((x >> 24) == 1 && (x & kSum) < n) {
-                    e = x & kSum;
-                    first = atomicMin(&state[e], part_of(v, P)) == kUnclaimed;
-                }
-            }
-            const uint32_t pos = block_append(&s_ltail, first, false);
-            if (first)
-                L.slots[pos].x = e;
-        }
-        if (tid == 0)
-            L.lstart[0] = 0;
-        __syncthreads();
-        uint32_t r = 0, lo = 0;
-        for (;;) {
-            // as in build_bucket: applying layer r claims round r + 1
-            const uint32_t hi = s_ltail;
-            __syncthreads();
-            if (tid == 0)
-                L.lstart[r + 1] = hi;
-            if (lo == hi)
-                break;
-            const uint32_t rr = (r + 1) << 2;
-            for (uint32_t base = lo; base < hi; base += kBlock) {
-                const uint32_t i = base + tid;
-                uint32_t c0 = 0, c1 = 0;
-                bool f0 = false, f1 = false;
-                if (i < hi) {
-                    const uint32_t e = L.slots[i].x;
-                    const uint32_t h = state[e] & 3u;
-                    const uint3 ev = bucket_edge(a, d, L, e, sd, P);
-                    const uint32_t vh = h == 0 ? ev.x : (h == 1 ? ev.y : ev.z);
-                    const uint32_t va = h == 0 ? ev.y : (h == 1 ? ev.z : ev.x);
-                    const uint32_t vb = h == 0 ? ev.z : (h == 1 ? ev.x : ev.y);
-                    L.slots[i] = make_uint3(vh, va, vb);
-                    const uint32_t oa = atomicSub(&rec[va], kOne32 + e);
-                    const uint32_t ob = atomicSub(&rec[vb], kOne32 + e);
-                    if ((oa >> 24) == 2) {
-                        c0 = (oa & kSum) - e;
-                        f0 = atomicMin(&state[c0], rr | part_of(va, P)) == kUnclaimed;
-                    }
-                    if ((ob >> 24) == 2) {
-                        c1 = (ob & kSum) - e;
-                        f1 = atomicMin(&state[c1], rr | part_of(vb, P)) == kUnclaimed;
-                    }
-                    if (!f0) {  // the first requested slot holds the first appended edge
-                        c0 = c1;
-                        f0 = f1;
-                        f1 = false;
-                    }
-                }
-                const uint32_t pos = block_append(&s_ltail, f0, f1);
-                if (f0)
-                    L.slots[pos].x = c0;
-                if (f1)
-                    L.slots[pos + 1].x = c1;
-            }
-            __syncthreads();
-            lo = hi;
-            r++;
-        }
-        nrounds = r;
-        const bool all = s_ltail == n;
-        __syncthreads();
-        if (all) {
-            ok = true;
-            break;
-        }
-    }
-    if (!ok) {
-        if (tid == 0)
-            write_result(d.result, sd, t < a.max_tries ? t + 1 : a.max_tries, status ? status : 1, nrounds);
-        __syncthreads();
-        return;
-    }
-    // assignment, last layer first, with the codes as bytes in LDS over the records
-    uint8_t* code8 = lds;
-    for (uint32_t v = tid; v < m; v += kBlock)
-        code8[v] = 0;
-    __syncthreads();
-    for (int32_t r = (int32_t)nrounds - 1; r >= 0; r--) {
-        const uint32_t lo = L.lstart[r], hi = L.lstart[r + 1];
-        for (uint32_t i = lo + tid; i < hi; i += kBlock) {
-            const uint3 sl = L.slots[i];
-            const uint32_t k = part_of(sl.x, P);
-            const uint32_t ca = code8[sl.y], cb = code8[sl.z];
-            const uint32_t g = (k + 6 - (ca == 3 ? 0 : ca) - (cb == 3 ? 0 : cb)) % 3;
-            code8[sl.x] = (uint8_t)(g ? g : 3);
-        }
-        __syncthreads();
-    }
-    pack_codes<kBlock>(code8, m, d, L);
-    if (tid == 0)
-        write_result(d.result, sd, t + 1, 0, nrounds);
-    __syncthreads();
-}
-
 // Waves per SIMD the launch shapes need resident: 1024 threads = 16 waves per compute unit, 512
 // two workgroups per compute unit, 256 three.
 template <int kBlock>
 constexpr int batch_waves_per_eu() { return kBlock >= 512 ? 4 : 3; }
 
+// The next bucket of queue `next` that `take` accepts, or a.B: the same for every thread, and known
+// to be, so that a bucket's sizes and pointers are kept in scalar registers.
+template <class Take>
+__device__ __forceinline__ uint32_t next_bucket(const BatchArgs& a, unsigned int* next, uint32_t* s_idx, Take take)
+{
+    if (threadIdx.x == 0) {
+        uint32_t idx;
+        do
+            idx = atomicAdd(next, 1u);
+        while (idx < a.B && !take(a.descs[a.order ? a.order[idx] : idx]));
+        *s_idx = idx < a.B ? idx : a.B;
+    }
+    __syncthreads();
+    const uint32_t idx = (uint32_t)__builtin_amdgcn_readfirstlane((int)*s_idx);
+    __syncthreads();
+    return idx;
+}
+
+// Builds buckets that fit in `bytes` of LDS until none is left (a.B) or one turns out not to fit
+// (its place in the queue: the caller sees to it).  kAlone: no bucket is another loop's.
+template <int kBlock, bool kClock, bool kAlone>
+__device__ __forceinline__ uint32_t build_lds_buckets(const BatchArgs& a, uint8_t* lds, uint32_t bytes, uint32_t* s_idx)
+{
+    for (;;) {
+        uint64_t t0 = 0;
+        if constexpr (kClock)
+            t0 = wall_clock64();
+        const uint32_t idx =
+            next_bucket(a, a.next + 1, s_idx, [&](const BucketDesc& d) { return kAlone || bucket_fits_lds(a, d.n, bytes); });
+        uint64_t t1 = 0;
+        if constexpr (kClock)
+            t1 = wall_clock64();
+        uint64_t n = 0;
+        bool left = false;
+        if (idx < a.B && kAlone)
+            left = !bucket_fits_lds(a, a.descs[a.order ? a.order[idx] : idx].n, bytes);
+        if (idx < a.B && !left) {
+            const BucketDesc d = a.descs[a.order ? a.order[idx] : idx];
+            n = d.n;
+            const uint64_t P = part_size_dev(n, a.gnum, a.gden);
+            const uint64_t total = d.keys ? 0 : d.offs[n];
+            auto fetch = [&](uint32_t i, uint64_t sd) -> ulonglong2 {
+                uint64_t x, y;
+                if (d.keys) {
+                    key_digest(a, d, i, sd, x, y);
+                } else {
+                    const uint64_t o0 = d.offs[i], o1 = d.offs[i + 1];
+                    digest_str(d.bytes, o0, o1 - o0, total, fin(sd + kGamma), fin(sd + 2 * kGamma), x, y);
+                }
+                return make_ulonglong2(x, y);
+            };
+            auto locals = [&](ulonglong2 key, uint64_t) -> uint3 { return digest_locals(key.x, key.y, P); };
+            const LdsOutcome out = lds_build<kBlock, true, 4>((uint32_t)n, (uint32_t)P, d.seed, a.max_tries, fetch,
+                                                              locals, lds, nullptr, nullptr, d.codes, d.rank);
+            left = out.status == kLdsTooDense;
+            if (threadIdx.x == 0 && !left)
+                write_result(d.result, out.seed, out.tries, out.status, out.rounds);
+        }
+        if constexpr (kClock) {
+            if (threadIdx.x == 0) {
+                atomicAdd(&g_batch_clock[kClQueue], (unsigned long long)(t1 - t0));
+                atomicAdd(&g_batch_clock[kClLds], (unsigned long long)(wall_clock64() - t1));
+                if (idx < a.B && !left) {
+                    atomicAdd(&g_batch_clock[kClLdsBuckets], 1ull);
+                    atomicAdd(&g_batch_clock[kClLdsKeys], (unsigned long long)n);
+                }
+            }
+        }
+        if (idx >= a.B || left)
+            return idx;
+    }
+}
+
+// Builds every bucket that fits in `bytes` of LDS but those whose degrees do not: these are marked.
+template <int kBlock, bool kClock, bool kAlone>
+__device__ __forceinline__ void build_all_lds_buckets(const BatchArgs& a, uint8_t* lds, uint32_t bytes, uint32_t* s_idx)
+{
+    uint32_t left = 0;
+    for (;;) {
+        const uint32_t idx = build_lds_buckets<kBlock, kClock, kAlone>(a, lds, bytes, s_idx);
+        if (idx >= a.B)
+            break;
+        left++;
+        if (threadIdx.x == 0)
+            a.descs[a.order ? a.order[idx] : idx].result->status = kStatusLeft;
+    }
+    if (threadIdx.x == 0 && left)
+        atomicAdd(a.next + 2, left);
+}
+
+// The same as a function of its own.  The arguments come by value and the LDS pointers with their
+// address space, so that neither ends up in memory.
+using LdsBytes = __attribute__((address_space(3))) uint8_t;
+template <int kBlock, bool kClock>
+__device__ __noinline__ void build_all_lds_buckets_call(BatchArgs a, LdsBytes* lds, LdsBytes* s_idx)
+{
+    build_all_lds_buckets<kBlock, kClock, false>(a, (uint8_t*)lds, a.lds_bytes, (uint32_t*)s_idx);
+}
+
+// Buckets too large for LDS first, then those that fit, in a function of its own behind the loop: in
+// one loop, or inlined, the two builds cost each other registers inside their own loops (records of
+// large buckets 7.9 to 8.2 ms a workgroup instead of 7.3).  With a.left_only, behind such a launch or one of k_batch_lds: what
+// that left.
 template <int kBlock, int kScope, bool kClock>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(batch_waves_per_eu<kBlock>())))
 void k_batch(BatchArgs a)
 {
     __shared__ uint32_t s_idx;
     __shared__ __align__(16) uint8_t s_lds[batch_lds_bytes<kBlock>()];
+    if (a.left_only && a.next[2] == 0)
+        return;
     uint8_t* slot = a.slots + (uint64_t)blockIdx.x * a.slot_bytes;
-    uint64_t t_life = 0, t_q = 0, t_queue = 0, t_lds = 0, n_lds = 0, k_lds = 0;
+    uint64_t t_life = 0, t_q = 0, t_queue = 0;
     if constexpr (kClock)
         t_life = wall_clock64();
     for (;;) {
         if constexpr (kClock)
             t_q = wall_clock64();
-        if (threadIdx.x == 0)
-            s_idx = atomicAdd(a.next, 1u);
-        __syncthreads();
-        const uint32_t idx = s_idx;
-        __syncthreads();
-        if constexpr (kClock) {
-            const uint64_t t2 = wall_clock64();
-            t_queue += t2 - t_q;
-            t_q = t2;
-        }
+        const uint32_t idx = next_bucket(a, a.left_only ? a.next + 3 : a.next, &s_idx, [&](const BucketDesc& d) {
+            return a.left_only ? d.result->status == kStatusLeft : !bucket_fits_lds(a, d.n, a.lds_bytes);
+        });
+        if constexpr (kClock)
+            t_queue += wall_clock64() - t_q;
         if (idx >= a.B)
             break;
         const BucketDesc d = a.descs[a.order ? a.order[idx] : idx];
-        const bool in_lds = d.n <= a.max_n && bucket_fits_lds<kBlock>(d.n, 3 * part_size_dev(d.n, a.gnum, a.gden));
-        if (in_lds && a.lds_path) {
-            build_bucket_lds<kBlock>(a, d, slot, s_lds);
-            if constexpr (kClock) {
-                t_lds += wall_clock64() - t_q;
-                n_lds++;
-                k_lds += d.n;
-            }
-        } else {
-            build_bucket<kBlock, kScope, kClock>(a, d, slot, s_lds);
-        }
+        build_bucket<kBlock, kScope, kClock>(a, d, slot, s_lds);
     }
+    if (a.lds_path && !a.left_only)
+        build_all_lds_buckets_call<kBlock, kClock>(a, (LdsBytes*)s_lds, (LdsBytes*)&s_idx);
     if constexpr (kClock) {
         if (threadIdx.x == 0) {
             atomicAdd(&g_batch_clock[kClQueue], (unsigned long long)t_queue);
-            atomicAdd(&g_batch_clock[kClLds], (unsigned long long)t_lds);
-            atomicAdd(&g_batch_clock[kClLdsBuckets], (unsigned long long)n_lds);
-            atomicAdd(&g_batch_clock[kClLdsKeys], (unsigned long long)k_lds);
             atomicAdd(&g_batch_clock[kClLife], (unsigned long long)(wall_clock64() - t_life));
         }
+    }
+}
+
+// A launch whose largest bucket fits in kBytes of LDS.
+template <int kBlock, uint32_t kBytes, bool kClock>
+__global__ __launch_bounds__(kBlock) void k_batch_lds(BatchArgs a)
+{
+    __shared__ uint32_t s_idx;
+    __shared__ __align__(16) uint8_t s_lds[kBytes];
+    uint64_t t_life = 0;
+    if constexpr (kClock)
+        t_life = wall_clock64();
+    build_all_lds_buckets<kBlock, kClock, true>(a, s_lds, kBytes, &s_idx);
+    if constexpr (kClock) {
+        if (threadIdx.x == 0)
+            atomicAdd(&g_batch_clock[kClLife], (unsigned long long)(wall_clock64() - t_life));
     }
 }
 
@@ -1315,10 +1265,26 @@ hipError_t launch_batch_descs(BucketDesc* descs, const uint64_t* keys, const uin
     return hipGetLastError();
 }
 
-hipError_t launch_batch(const BatchArgs& a, unsigned block, unsigned grid, bool wg_scope, hipStream_t s)
+// A launch whose buckets all fit in LDS, on the compute units that the caller's launch shape covers:
+// the rounds leave most of a compute unit idle, so smaller buckets share one, as many workgroups
+// as their LDS allows.
+static hipError_t launch_batch_lds(const BatchArgs& a, uint32_t bytes, unsigned cus, hipStream_t s)
 {
-    hipError_t err = launch_zero(a.next, sizeof(unsigned int), s);
-    if (err != hipSuccess) return err;
+#define MPHX_LDS(BLOCK, KB, PER)                                                 \
+    a.clock ? k_batch_lds<BLOCK, KB * 1024, true><<<cus * PER, BLOCK, 0, s>>>(a) \
+            : k_batch_lds<BLOCK, KB * 1024, false><<<cus * PER, BLOCK, 0, s>>>(a)
+    if (bytes <= 38 * 1024)
+        MPHX_LDS(256, 38, 4);
+    else if (bytes <= 78 * 1024)
+        MPHX_LDS(512, 78, 2);
+    else
+        MPHX_LDS(1024, 158, 1);
+#undef MPHX_LDS
+    return hipGetLastError();
+}
+
+static hipError_t launch_batch_kernel(const BatchArgs& a, unsigned block, unsigned grid, bool wg_scope, hipStream_t s)
+{
     constexpr int W = __HIP_MEMORY_SCOPE_WORKGROUP, A = __HIP_MEMORY_SCOPE_AGENT;
     if (a.clock) {  // the instantiation that clocks its phases
         switch (block) {
@@ -1345,6 +1311,25 @@ hipError_t launch_batch(const BatchArgs& a, unsigned block, unsigned grid, bool 
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_batch(const BatchArgs& args, unsigned block, unsigned grid, bool wg_scope, hipStream_t s)
+{
+    BatchArgs a = args;
+    hipError_t err = launch_zero(a.next, 4 * sizeof(unsigned int), s);
+    if (err != hipSuccess) return err;
+    const unsigned __int128 num = (unsigned __int128)a.max_n * a.gnum, den = (unsigned __int128)3 * a.gden;
+    const uint64_t m = 3 * (uint64_t)((num + den - 1) / den);
+    const uint32_t bytes = m <= kLdsMaxVertices ? lds_build_bytes((uint32_t)m, true) : ~0u;
+    if (a.lds_path && bytes <= 158 * 1024) {
+        err = launch_batch_lds(a, bytes, std::max(1u, (unsigned)((uint64_t)grid * block / 1024)), s);
+    } else {
+        a.lds_bytes = block == 1024 ? batch_lds_bytes<1024>() : (block == 512 ? batch_lds_bytes<512>() : batch_lds_bytes<256>());
+        err = launch_batch_kernel(a, block, grid, wg_scope, s);
+    }
+    if (err != hipSuccess || !a.lds_path) return err;
+    a.left_only = 1;  // ends at once unless a bucket was left
+    return launch_batch_kernel(a, block, grid, wg_scope, s);
 }
 
 hipError_t batch_clock_read(uint64_t* out, int max_entries, bool reset)

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "common.h"
+#include "lds_build.h"
 
 namespace mphx {
 
@@ -139,6 +140,7 @@ hipError_t launch_rounds_again(const PeelState& st, hipStream_t s);
 // launch_rounds before its outcome is known, does nothing after an incomplete peel.
 // st.sync[1] is zeroed: by launch_run_init, else by launch_sync_zero.
 hipError_t launch_sync_zero(const PeelState& st, hipStream_t s);
+hipError_t launch_copy_ctrl(const Ctrl* ctrl, Ctrl* out, hipStream_t s);
 hipError_t launch_mphf_finish(const PeelState& st, uint32_t nrounds, uint64_t* codes, uint64_t* rank, uint32_t* bcount,
                               hipStream_t s);
 hipError_t launch_sf_solve(const PeelState& st, uint32_t nrounds, uint64_t sigma, uint32_t b, hipStream_t s);
@@ -148,6 +150,23 @@ uint64_t sort_tiles(uint64_t n);
 hipError_t launch_order_sort(const uint32_t* round, uint64_t n, uint32_t nrounds, uint32_t* order,
                              uint32_t* scratch_ids, uint32_t* tilehist, void* scan_scratch, size_t scan_bytes,
                              hipStream_t s);
+
+// One MPHF build in one workgroup, all tries (small.hip); out: host-visible or device memory.
+struct SmallArgs {
+    const uint64_t* keys;   // u64 keys, or null
+    const uint8_t* bytes;   // string keys
+    const uint64_t* offs;
+    const uint32_t* edges;  // string keys' edges under the first seed (nullable)
+    uint32_t n, P;
+    uint64_t seed;
+    uint32_t max_tries;
+    uint16_t* queue;        // m entries
+    uint32_t* start;        // n + 2 entries
+    uint64_t *codes, *rank;
+    LdsOutcome* out;
+};
+bool small_build_fits(uint64_t n, uint64_t m);
+hipError_t launch_small_build(const SmallArgs& a, hipStream_t s);
 
 // assignment, ranking, lookup (solve.hip)
 // 2-core edges of a failed try: their count (ctrl->aux), then pairs with equal vertex triples

@@ -535,6 +535,18 @@ hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, hi
     return hipGetLastError();
 }
 
+__global__ void k_copy_ctrl(const uint64_t* __restrict__ ctrl, uint64_t* __restrict__ out)
+{
+    if (threadIdx.x < sizeof(Ctrl) / 8)
+        out[threadIdx.x] = ctrl[threadIdx.x];
+}
+
+hipError_t launch_copy_ctrl(const Ctrl* ctrl, Ctrl* out, hipStream_t s)
+{
+    k_copy_ctrl<<<1, 64, 0, s>>>(reinterpret_cast<const uint64_t*>(ctrl), reinterpret_cast<uint64_t*>(out));
+    return hipGetLastError();
+}
+
 hipError_t launch_sync_zero(const PeelState& st, hipStream_t s) { return launch_zero(st.sync, run_sync_bytes(), s); }
 hipError_t launch_rounds_again(const PeelState& st, hipStream_t s) { return launch_sync_zero(st, s); }
 

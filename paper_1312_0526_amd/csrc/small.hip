@@ -1,0 +1,64 @@
+// One small MPHF build in one workgroup and one launch, retries included (lds_build.h).
+#include "launch.h"
+#include "lds_build.h"
+
+namespace mphx {
+
+template <int kBlock, uint32_t kBytes, bool kQueueLds>
+__global__ __launch_bounds__(kBlock) void k_small_build(SmallArgs a)
+{
+    __shared__ __align__(16) uint8_t s_lds[kBytes];
+    const uint64_t total = a.keys ? 0 : a.offs[a.n];
+    const uint64_t P = a.P;
+    // u64 keys as they are; strings as their digest, or as their hashed edge
+    auto fetch = [&](uint32_t i, uint64_t sd) -> ulonglong2 {
+        if (a.keys)
+            return make_ulonglong2(a.keys[i], 0);
+        if (a.edges && sd == a.seed) {
+            const uint32_t* t = a.edges + 3 * (uint64_t)i;
+            return make_ulonglong2(t[0] | (uint64_t)t[1] << 32, t[2]);
+        }
+        const uint64_t o0 = a.offs[i], o1 = a.offs[i + 1];
+        uint64_t x, y;
+        digest_str(a.bytes, o0, o1 - o0, total, fin(sd + kGamma), fin(sd + 2 * kGamma), x, y);
+        return make_ulonglong2(x, y);
+    };
+    auto locals = [&](ulonglong2 key, uint64_t sd) -> uint3 {
+        uint64_t x = key.x, y = key.y;
+        if (a.keys)
+            x = y = key.x ^ sd;
+        else if (a.edges && sd == a.seed)
+            return make_uint3((uint32_t)x, (uint32_t)(x >> 32) - a.P, (uint32_t)y - 2 * a.P);
+        return make_uint3((uint32_t)range_reduce(fin(x + kGamma), P), (uint32_t)range_reduce(fin(x + 2 * kGamma), P),
+                          (uint32_t)range_reduce(fin(y + 3 * kGamma), P));
+    };
+    const LdsOutcome out = lds_build<kBlock, kQueueLds, 4>(a.n, a.P, a.seed, a.max_tries, fetch, locals, s_lds, a.queue,
+                                                           a.start, a.codes, a.rank);
+    if (threadIdx.x == 0)
+        *a.out = out;
+}
+
+// Up to 7 bytes of LDS per vertex with the queue in LDS, 5 without.  256 threads while a
+// round's queue (a quarter of the vertices at most, in practice) is a few waves: their barriers cost
+// less than those of 1024.
+constexpr uint32_t kSmallBytes = 24 * 1024, kLargeBytes = 158 * 1024;
+
+bool small_build_fits(uint64_t n, uint64_t m)
+{
+    return n < 0xFFFFFFFFull && m <= kLdsMaxVertices && lds_build_bytes((uint32_t)m, false) <= kLargeBytes;
+}
+
+hipError_t launch_small_build(const SmallArgs& a, hipStream_t s)
+{
+    const uint32_t m = 3 * a.P;
+    if (!small_build_fits(a.n, m)) return hipErrorInvalidValue;
+    if (lds_build_bytes(m, true) <= kSmallBytes)
+        k_small_build<256, kSmallBytes, true><<<1, 256, 0, s>>>(a);
+    else if (lds_build_bytes(m, true) <= kLargeBytes)
+        k_small_build<1024, kLargeBytes, true><<<1, 1024, 0, s>>>(a);
+    else
+        k_small_build<1024, kLargeBytes, false><<<1, 1024, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+}  // namespace mphx
