@@ -195,7 +195,7 @@ __device__ uint32_t lds_exclusive_scan(uint32_t* a, uint32_t count, uint32_t* wt
 template <int kBlock>
 constexpr uint32_t batch_tile() { return kBlock >= 1024 ? 8192u : 4096u; }
 constexpr uint32_t kBatchMaxBuckets = 2048;
-// LDS of the partitioned record build's tile, counts and bounds, or a whole bucket's graph: 1024-thread
+// LDS of the partitioned record build's tile, counts and bounds, then of the codes: 1024-thread
 // workgroups take 158 KB (one per compute unit), 512-thread ones 78 KB (two), 256-thread ones 48 KB
 // (three).
 template <int kBlock>
@@ -273,10 +273,12 @@ __device__ __forceinline__ void write_result(BucketResult* r, uint64_t seed_used
     r->n_rounds = rounds;
 }
 
-// Codes (one byte per vertex, code8) packed 2 bits per vertex into
-// d.codes, counted per 512 vertices and scanned into the rank samples d.rank.
+// Codes of m vertices -- those below `in_lds` (a multiple of 512, or all) 2 bits each in LDS words,
+// the others one byte each in device memory -- packed 2 bits per vertex into d.codes, counted per
+// 512 vertices and scanned into the rank samples d.rank.
 template <int kBlock>
-__device__ void pack_codes(const uint8_t* code8, uint32_t m, const BucketDesc& d, const SlotLayout& L)
+__device__ void pack_codes(const uint32_t* lds_codes, uint32_t in_lds, const uint8_t* code8, uint32_t m,
+                           const BucketDesc& d, const SlotLayout& L)
 {
     const uint32_t tid = threadIdx.x;
     const uint32_t nwords = (m + 31) / 32, nblocks = (m + 511) / 512;
@@ -284,7 +286,9 @@ __device__ void pack_codes(const uint8_t* code8, uint32_t m, const BucketDesc& d
         uint32_t w = base + tid;
         uint64_t x = 0;
         if (w < nwords) {
-            if (32 * w + 32 <= m) {
+            if (32 * w < in_lds) {  // the codes past m are zero
+                x = lds_codes[2 * w] | (uint64_t)lds_codes[2 * w + 1] << 32;
+            } else if (32 * w + 32 <= m) {
                 const uint4* p = reinterpret_cast<const uint4*>(code8 + 32 * w);
                 uint4 q0 = p[0], q1 = p[1];
                 uint32_t dw[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
@@ -1048,24 +1052,39 @@ __device__ void build_bucket(const BatchArgs& a, const BucketDesc& d, uint8_t* s
         clk.flush(n, t < a.max_tries ? t + 1 : a.max_tries, nrounds);
         return;
     }
-    // assignment, last layer first; codes as bytes in the record area
-    uint8_t* code8 = reinterpret_cast<uint8_t*>(L.rec);
-    for (uint32_t v = tid; v < m; v += kBlock)
+    // Assignment, last layer first.  As many codes as fit are kept in LDS, 2 bits each (a hinge's
+    // code is written once, over a zero), the others as bytes in the record area: the three random
+    // accesses of an edge run at the device's ceiling (94 G/s) from bytes in device memory alone,
+    // and only a bucket beyond 526,000 keys still makes some (1024 threads).
+    constexpr uint32_t kLdsCodes = batch_lds_bytes<kBlock>() / 128 * 512;  // 4 codes a byte, whole rank blocks
+    uint32_t* const codes2 = reinterpret_cast<uint32_t*>(lds);
+    uint8_t* const code8 = reinterpret_cast<uint8_t*>(L.rec);
+    const uint32_t in_lds = m <= kLdsCodes ? (m + 511) & ~511u : kLdsCodes;
+    for (uint32_t w = tid; w < in_lds / 16; w += kBlock)
+        codes2[w] = 0;
+    for (uint32_t v = in_lds + tid; v < m; v += kBlock)
         code8[v] = 0;
     __syncthreads();
+    auto code_of = [&](uint32_t v) -> uint32_t {
+        return v < in_lds ? codes2[v >> 4] >> (2 * (v & 15)) & 3u : (uint32_t)code8[v];
+    };
     for (int32_t r = (int32_t)nrounds - 1; r >= 0; r--) {
         const uint32_t lo = L.lstart[r], hi = L.lstart[r + 1];
         for (uint32_t i = lo + tid; i < hi; i += kBlock) {
             uint3 sl = L.slots[i];
             uint32_t k = part_of(sl.x, P);
-            uint32_t ca = code8[sl.y], cb = code8[sl.z];
+            uint32_t ca = code_of(sl.y), cb = code_of(sl.z);
             uint32_t g = (k + 6 - (ca == 3 ? 0 : ca) - (cb == 3 ? 0 : cb)) % 3;
-            code8[sl.x] = (uint8_t)(g ? g : 3);
+            g = g ? g : 3;
+            if (sl.x < in_lds)
+                atomicOr(&codes2[sl.x >> 4], g << (2 * (sl.x & 15)));
+            else
+                code8[sl.x] = (uint8_t)g;
         }
         __syncthreads();
     }
     clk.mark(kClAssign);
-    pack_codes<kBlock>(code8, m, d, L);
+    pack_codes<kBlock>(codes2, in_lds, code8, m, d, L);
     if (tid == 0)
         write_result(d.result, sd, t + 1, 0, nrounds);
     __syncthreads();

@@ -1,5 +1,6 @@
 """Builds whose hypergraph lives in LDS -- single small builds and the buckets of batched launches --
-against the oracle (GPU only), at the edges of what fits."""
+and the code table that larger buckets keep partly in LDS, against the oracle (GPU only), at the
+edges of what fits."""
 import numpy as np
 import pytest
 
@@ -126,3 +127,16 @@ def test_batched_lds_edges(mx, o, block, kb, alone):
             assert res[b]["n_rounds"] == want["n_rounds"], b
             assert np.array_equal(words(bb.bucket_codes(b)), want["words"]), b
             assert np.array_equal(words(bb.bucket_rank(b)), want["rank"]), b
+
+
+@pytest.mark.parametrize("block,vertices", [(256, 196_608), (512, 319_488), (1024, 647_168)])
+def test_batched_codes_partly_in_lds(mx, o, block, vertices):
+    edge = keys_with(vertices)
+    sizes = [edge - 200, edge, edge + 3, edge + 5000]
+    sets = [workloads.u64_keys(n, gen_seed=n + 1) for n in sizes]
+    bb, res = batch(mx, sets, block=block)
+    for b, keys in enumerate(sets):
+        status, want = o.mphf_build_u64(keys, seed=0)
+        assert status == oracle.OK and res[b]["status"] == 0
+        assert np.array_equal(words(bb.bucket_codes(b)), want["words"]), b
+        assert np.array_equal(words(bb.bucket_rank(b)), want["rank"]), b
