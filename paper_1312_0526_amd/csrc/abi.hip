@@ -661,18 +661,27 @@ int mphx_peel(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t* order, ui
     st.sync = L.sync;
     st.rcap = round_cap(n);
 
-    HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
-    HIP_TRY(launch_fill_u32(L.state, n, kUnclaimed, s));
     const bool grid_run = n <= kRunMaxEdges;
-    HIP_TRY(grid_run ? launch_run_init(st, s) : launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
+    const uint32_t bins = bins_shift(n, m, st.rcap);  // grid_run where not 0
+    if (!bins) {
+        HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
+        HIP_TRY(launch_fill_u32(L.state, n, kUnclaimed, s));
+    }
+    HIP_TRY(grid_run ? launch_run_init(st, bins ? bins_zero_words(m, bins) : 1, s)
+                     : launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
     if (!grid_run) HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
     {
         Timed t(PH_BUILD, s);
-        HIP_TRY(launch_edges_build(edges, n, m, L.rec, L.ctrl, s));
+        if (bins) {
+            HIP_TRY(launch_bins_scatter(st, bins, nullptr, 0, s));
+            HIP_TRY(launch_bins_accum(st, bins, s));
+        } else {
+            HIP_TRY(launch_edges_build(edges, n, m, L.rec, L.ctrl, s));
+        }
     }
     {
         Timed t(PH_FRONTIER, s);
-        HIP_TRY(launch_round0(st, s));
+        HIP_TRY(bins ? launch_bins_round0(st, bins, s) : launch_round0(st, s));
     }
     uint64_t f0 = 0, peeled = 0;
     Ctrl h;
@@ -747,7 +756,7 @@ int mphx_peel_r(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t r, uint3
     HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
     HIP_TRY(launch_fill_u32(L.state, n, kUnclaimed, s));
     const bool grid_run = n <= kRunMaxEdges;
-    HIP_TRY(grid_run ? launch_run_init(st, s) : launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
+    HIP_TRY(grid_run ? launch_run_init(st, 1, s) : launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
     if (!grid_run) HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
     {
         Timed t(PH_BUILD, s);
@@ -1047,7 +1056,9 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
     MphfLayout L;
     layout_mphf(c, n, m, lists, L, sf != nullptr);
     uint32_t t0 = 0;  // the first try that is left to do
-    const bool part = g_opt.part_build.load() > 0 && n >= (1ull << g_opt.part_build.load());  // part_build <= 32
+    const int pb = g_opt.part_build.load();  // <= 32
+    const uint32_t bins = pb > 1 && !lists ? bins_shift(n, m, round_cap(n)) : 0;
+    const bool part = !bins && pb > 0 && n >= (1ull << pb);
     if (!sf && !lists && !part && g_opt.grid.load() == 0 && small_build_fits(n, m)) {
         int rc = small_build(k, n, seed, P, max_tries, codes, rank, L, s, info, t0);
         if (rc || t0 == 0) return rc;
@@ -1097,34 +1108,41 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
     };
     for (t = t0; t < max_tries; t++) {
         uint64_t sd = seed + t;
-        if (!part)
+        if (!part && !bins)
             HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
         grid_run = !st.lists && n <= kRunMaxEdges;
         if (grid_run) {
-            HIP_TRY(launch_run_init(st, s));
+            HIP_TRY(launch_run_init(st, bins ? bins_zero_words(m, bins) : 1, s));
         } else {
             HIP_TRY(launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
             HIP_TRY(launch_zero(L.ccount, 2 * (st.rcap + 2) * sizeof(unsigned long long), s));
             HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
         }
         {
-            // with the partitioned build the hash only writes the edges
+            // with the partitioned build, and before the bins, the hash only writes the edges
             Timed tm(PH_HASH, s);
-            uint64_t* fused = part ? nullptr : L.rec;
+            uint64_t* fused = part || bins ? nullptr : L.rec;
             const PartHist1 h1 = part ? part_hist1(L.aux, n, P) : PartHist1{nullptr, 0, 0};
-            if (k.kind == MPHX_KEYS_U64)
+            if (bins && k.kind == MPHX_KEYS_U64)
+                HIP_TRY(launch_bins_scatter(st, bins, k.keys, sd, s));
+            else if (k.kind == MPHX_KEYS_U64)
                 HIP_TRY(launch_hash_u64(k.keys, n, sd, P, L.edges, fused, h1, s));
             else
                 HIP_TRY(launch_hash_str(k.bytes, k.offs, n, sd, P, L.edges, fused, h1, s));
         }
-        if (part) {
+        if (bins) {
+            Timed tm(PH_BUILD, s);
+            if (k.kind == MPHX_KEYS_STR)
+                HIP_TRY(launch_bins_scatter(st, bins, nullptr, 0, s));
+            HIP_TRY(launch_bins_accum(st, bins, s));
+        } else if (part) {
             Timed tm(PH_BUILD, s);
             // the claim buffers (m >= n pairs each) are free until the rounds
             HIP_TRY(launch_part_build(L.edges, n, P, L.rec, L.pairs1, L.pairs2, L.claims, L.claims_tmp, L.aux, s));
         }
         // atomic claims keep per-edge states (after the build: they share the pair buffers);
         // claim lists carry the hinge in the layer slots from round 0 on
-        if (!st.lists)
+        if (!st.lists && !bins)
             HIP_TRY(launch_fill_u32(L.state, n, kUnclaimed, s));
         st.round0_updates = st.lists && g_opt.update_lists.load() > 0;
         if (sf) {
@@ -1135,7 +1153,7 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
         }
         {
             Timed tm(PH_FRONTIER, s);
-            HIP_TRY(launch_round0(st, s));
+            HIP_TRY(bins ? launch_bins_round0(st, bins, s) : launch_round0(st, s));
         }
         uint64_t f0 = 0;
         int rc;

@@ -44,7 +44,7 @@ struct PeelState {
     const uint32_t* vin;
     uint32_t* vout;
     void* aux;              // partition histograms and scan scratch (part_aux_bytes)
-    struct GridSync* sync;  // two groups' barrier state (rounds.hip)
+    struct GridSync* sync;  // three groups' barrier state (rounds.hip, bins.hip)
 };
 
 // utilities (scan.hip)
@@ -93,6 +93,17 @@ hipError_t launch_claims_resolve(const PeelState& st, uint32_t r, uint64_t count
 // r + 1 into st.claims_tmp through ccount[r + 1].
 hipError_t launch_update_apply(const PeelState& st, uint32_t r, uint64_t count, hipStream_t s);
 
+// Binned record build of mid-sized runs, and round 0 from it (bins.hip).  bins_shift: vertices of a
+// bucket as a power of two, or 0 where the build does not apply.  The working memory is st.lcount
+// (rcap + 2 words), whose first bins_zero_words the run's start clears, and the 16n bytes from st.slots (slots and
+// states); launch_bins_scatter hashes u64 keys into st.edges as it goes, or reads st.edges (keys nullptr) and
+// checks them unless they are tripartite; launch_bins_round0 writes every edge's state and layer 0.
+uint32_t bins_shift(uint64_t n, uint64_t m, uint64_t rcap);
+uint64_t bins_zero_words(uint64_t m, uint32_t shift);
+hipError_t launch_bins_scatter(const PeelState& st, uint32_t shift, const uint64_t* keys, uint64_t seed, hipStream_t s);
+hipError_t launch_bins_accum(const PeelState& st, uint32_t shift, hipStream_t s);
+hipError_t launch_bins_round0(const PeelState& st, uint32_t shift, hipStream_t s);
+
 // hashing and key generation (keys.hip); rec == nullptr hashes only
 // h1.hist != nullptr (with rec == nullptr): also count the first-pass partition digits
 hipError_t launch_hash_u64(const uint64_t* keys, uint64_t n, uint64_t seed, uint64_t P, uint32_t* edges,
@@ -132,7 +143,7 @@ hipError_t launch_apply(const PeelState& st, uint32_t r, bool hinge_in_slot, App
 // workgroups keep more of them in flight.
 constexpr uint64_t kRunMaxEdges = 1ull << 24;  // (27-bit counts in a barrier's payload)
 size_t run_sync_bytes();
-hipError_t launch_run_init(const PeelState& st, hipStream_t s);
+hipError_t launch_run_init(const PeelState& st, uint64_t zero_words, hipStream_t s);
 hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, hipStream_t s);
 hipError_t launch_rounds_again(const PeelState& st, hipStream_t s);
 // All layers of a complete peel of nrounds rounds in one launch, any size; the MPHF's codes and

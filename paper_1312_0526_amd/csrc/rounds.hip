@@ -25,18 +25,19 @@ constexpr uint32_t kPrivate = 4096;          // edges of a workgroup's own list
 constexpr uint32_t kRoundsPerLaunch = 1024;  // a longer peel goes on in another launch
 
 __global__ __launch_bounds__(256) void k_run_init(Ctrl* ctrl, uint64_t* lstart, unsigned long long* lcount,
-                                                  GridSync* sync, uint32_t nsync)
+                                                  GridSync* sync, uint32_t nsync, uint64_t zero_words)
 {
     unsigned long long* w = reinterpret_cast<unsigned long long*>(sync);
     for (uint32_t i = threadIdx.x; i < nsync * (sizeof(GridSync) / 8); i += 256)
         w[i] = 0;
     if (threadIdx.x < sizeof(Ctrl) / 8)
         reinterpret_cast<uint64_t*>(ctrl)[threadIdx.x] = 0;
+    for (uint64_t i = threadIdx.x; i < zero_words; i += 256)
+        lcount[i] = 0;
     __syncthreads();
     if (threadIdx.x == 0) {
         ctrl->nrounds = 0xFFFFFFFFu;
         lstart[0] = 0;
-        lcount[0] = 0;
     }
 }
 
@@ -482,7 +483,7 @@ __global__ __launch_bounds__(kRoundsBlock) void k_sf_solve(const uint3* __restri
 }
 
 // ------------------------------------------------------------------------------------------
-size_t run_sync_bytes() { return 2 * sizeof(GridSync); }
+size_t run_sync_bytes() { return 3 * sizeof(GridSync); }
 
 // Members of a group for n edges.  Few make the barrier cheap (0.8 us at 8 members, 1.3 at 64), many
 // hide the latency of the large first rounds; whole builds of u64 keys took, in us:
@@ -500,9 +501,9 @@ static unsigned run_grid(const PeelState& st)
     return (unsigned)std::min<uint64_t>(std::max<uint64_t>(g, 1), kGridMax);
 }
 
-hipError_t launch_run_init(const PeelState& st, hipStream_t s)
+hipError_t launch_run_init(const PeelState& st, uint64_t zero_words, hipStream_t s)
 {
-    k_run_init<<<1, 256, 0, s>>>(st.ctrl, st.lstart, st.lcount, st.sync, 2);
+    k_run_init<<<1, 256, 0, s>>>(st.ctrl, st.lstart, st.lcount, st.sync, 3, zero_words);
     return hipGetLastError();
 }
 
