@@ -34,7 +34,7 @@ struct GridSync {
     GridLine ticket;      // tickets taken; bit 31 once the group is closed
     GridLine members;     // group size, 0 until closed
     GridLine ring[4][1 + kGridSub];  // barrier words: ring[phase % 4] = root, then the subgroups
-    GridLine cursor[2];   // append cursors of the launch
+    GridLine cursor[3];   // append cursors of the launch
     unsigned long long sums[kGridMax];  // one word per member
 };
 
@@ -92,9 +92,10 @@ __device__ __forceinline__ bool grid_join(GridSync* s, Grid& g, uint32_t* lds)
 // All members arrive; each gives a payload (below 2^54 in total), which thread 0 computes once
 // the workgroup's threads have met, and every thread gets the sum.  Between arriving and waiting
 // every thread runs overlap(): loads of what no member changes, stores that no member reads in
-// this launch.  `lds` is one word of the workgroup's own.
-template <class Payload, class Overlap>
-__device__ __forceinline__ uint64_t grid_barrier(Grid& g, uint64_t* lds, Payload payload, Overlap overlap)
+// this launch.  leave() is thread 0's, before the workgroup goes on.  `lds` is one word of the
+// workgroup's own.
+template <class Payload, class Overlap, class Leave>
+__device__ __forceinline__ uint64_t grid_barrier(Grid& g, uint64_t* lds, Payload payload, Overlap overlap, Leave leave)
 {
     constexpr uint64_t kCount = (1ull << kGridArrive) - 1;
     drain_memory();
@@ -136,10 +137,16 @@ __device__ __forceinline__ uint64_t grid_barrier(Grid& g, uint64_t* lds, Payload
             }
         }
         *lds = total;
+        leave();
     }
     g.phase++;
     __syncthreads();
     return *lds;
+}
+template <class Payload, class Overlap>
+__device__ __forceinline__ uint64_t grid_barrier(Grid& g, uint64_t* lds, Payload payload, Overlap overlap)
+{
+    return grid_barrier(g, lds, payload, overlap, [] {});
 }
 __device__ __forceinline__ void grid_barrier(Grid& g, uint64_t* lds)
 {

@@ -10,7 +10,9 @@
 // claim, the barrier.  So the next layer never leaves the compute unit that found it: each
 // workgroup keeps the edges it claimed first in a list of its own in LDS and deletes them itself
 // in the next round.  Claims beyond the list's size, and round 0's layer, go through a list in
-// device memory that all members share.  The order of a layer's slots is free (Section 4.2), and
+// device memory that all members share.  A plateau round of 4,000 edges at 10^6 keys takes 4.1 us with
+// 122 members, 1.65 of them the barrier; layers above some 50,000 edges are bound by the device's atomics
+// (20 G/s).  The order of a layer's slots is free (Section 4.2), and
 // the layers come out back to back as the other paths write them.
 #include "common.h"
 #include "grid.h"
@@ -22,6 +24,11 @@ namespace mphx {
 
 constexpr uint32_t kRoundsBlock = 512;
 constexpr uint32_t kPrivate = 4096;          // edges of a workgroup's own list
+// Every so many rounds all edges of the next layer go through the shared list, which deals them out
+// evenly: the private lists grow by descent, and without it one of 122 workgroups held 4 times its
+// share of a layer after 50 rounds at 10^6 keys.  The rounds took 397, 386, 385 and 412 us with a deal
+// every 4, 8, 16 and 32 rounds there, 427 without.
+constexpr uint32_t kDealRounds = 16;
 constexpr uint32_t kRoundsPerLaunch = 1024;  // a longer peel goes on in another launch
 
 __global__ __launch_bounds__(256) void k_run_init(Ctrl* ctrl, uint64_t* lstart, unsigned long long* lcount,
@@ -107,9 +114,11 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
             c->layer0 = glist;
         }
     }
-    unsigned long long* const pcur = &a.sync->cursor[0].w;  // edges of private lists, all rounds
-    unsigned long long* const gcur = &a.sync->cursor[1].w;  // edges of shared lists, all rounds
-    uint64_t psum = 0, gsum = 0;  // what the cursors passed before this round
+    // Edges of private lists, a cursor for even and one for odd rounds: a member moves it after it has
+    // arrived, so others may be one round ahead of it, but not two.
+    GridLine* const pcur = a.sync->cursor;
+    unsigned long long* const gcur = &a.sync->cursor[2].w;  // edges of shared lists, all rounds
+    uint64_t psum = 0, pother = 0, gsum = 0;  // what the cursors passed before this round
     uint64_t ptot = 0;            // this layer's private edges
     uint32_t pc = 0, cur = 0, done = 0;
     uint64_t pbase = 0;
@@ -139,7 +148,7 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
             break;
         }
         // the last round of a launch leaves the next layer in the shared list
-        const uint32_t cap = done + 1 == kRoundsPerLaunch ? 0u : kPrivate;
+        uint32_t cap = done + 1 == kRoundsPerLaunch ? 0u : kPrivate;
         const uint32_t rr = (r + 1) << kShift;
         uint32_t* const next = s_list[cur ^ 1];
         uint32_t* const count = &s_next[cur ^ 1];
@@ -224,14 +233,23 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
             peel(s_list[cur][i], pbase + i);
         for (uint64_t j = member_first(g); j < glist; j += member_stride(g))
             peel(ag_load(&a.slots[lo + j].x), lo + j);
+        if (g.members > 1 && done % kDealRounds == kDealRounds - 1) {
+            __syncthreads();
+            const uint32_t p = min(*count, cap);
+            if (tid == 0)
+                s_off = p ? ag_add(gcur, p) : 0ull;
+            __syncthreads();
+            for (uint32_t i = tid; i < p; i += kRoundsBlock)
+                ag_store(&a.slots[hi + (s_off - gsum) + i].x, next[i]);
+            cap = 0;
+        }
         uint32_t pnext = 0;
+        uint64_t off = 0;
         const uint64_t total = grid_barrier(
             g, &s_total,
             [&]() -> uint64_t {
                 const uint32_t k = *count, p = min(k, cap);
                 s_next[cur] = 0;
-                // where this workgroup's private edges of the next layer go, asked for ahead
-                s_off = p ? ag_add(pcur, p) : 0ull;
                 return (uint64_t)p | (uint64_t)(k - p) << 27;
             },
             [&] {
@@ -243,19 +261,26 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
                     }
                 }
                 pnext = min(*count, cap);
+                // where this workgroup's private edges of the next layer go; nobody waits for it
+                // before the group has met
+                if (tid == 0 && pnext)
+                    off = ag_add(&pcur[done & 1].w, pnext);
                 if (tid < pnext) {
                     e0 = next[tid];
 #pragma unroll
                     for (uint32_t q = 0; q < kR; q++)
                         v0[q] = a.edges[(uint64_t)kR * e0 + q];
                 }
-            });
+            },
+            [&] { s_off = off; });
         lo = hi;
         ptot = total & ((1ull << 27) - 1);
         glist = total >> 27;
         pc = pnext;
         pbase = lo + glist + (s_off - psum);
-        psum += ptot;
+        const uint64_t passed = psum + ptot;
+        psum = pother;
+        pother = passed;
         gsum += glist;
         cur ^= 1;
     }
@@ -488,11 +513,11 @@ size_t run_sync_bytes() { return 3 * sizeof(GridSync); }
 // Members of a group for n edges.  Few make the barrier cheap (0.8 us at 8 members, 1.3 at 64), many
 // hide the latency of the large first rounds; whole builds of u64 keys took, in us:
 //   members            8     16     32     64    128    192    256
-//   10^5 keys        614    535    522    560    573    592    608
-//   3x10^5          1080    832    730    754    769    807    829
-//   10^6            2441   1529   1112    980    954   1001   1044
-//   3x10^6          6307   3550   2344   1787   1532   1551   1597
-//   10^7           22579  11894   7325   5286   3965   3565   3374
+//   10^5 keys        556    487    472    490    543    564    576
+//   3x10^5           934    705    607    606    654    700    714
+//   10^6            2175   1279    870    734    714    735    750
+//   3x10^6          5891   3139   1907   1346   1174   1174   1180
+//   9x10^6         18971   9761   5891   4012   2927   2655   2582
 static unsigned run_grid(const PeelState& st)
 {
     const uint64_t n = st.n;

@@ -85,3 +85,31 @@ def test_path_beyond_one_launch(mx, n):
     i = np.arange(n)
     assert got["n_rounds"] == (n + 1) // 2 and got["n_peeled"] == n
     assert np.array_equal(words(got["round"], np.uint32), np.minimum(i, n - 1 - i))
+
+
+# groups of several builds at once, whose members fall far behind one another
+@pytest.mark.parametrize("n", [40_001, 250_003, 1_000_003])
+def test_builds_side_by_side(mx, n):
+    import threading
+
+    import torch
+
+    keys = [dev(workloads.u64_keys(n + i, gen_seed=n + i)) for i in range(6)]
+    want = [mx.mphf_build_u64(k, seed=1) for k in keys]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(8):
+                got = mx.mphf_build_u64(keys[i], seed=1)
+                torch.cuda.current_stream().synchronize()
+                if not (torch.equal(got["codes"], want[i]["codes"]) and torch.equal(got["rank"], want[i]["rank"])):
+                    wrong.append(i)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
