@@ -1138,19 +1138,21 @@ __device__ __forceinline__ uint32_t build_lds_buckets(const BatchArgs& a, uint8_
             n = d.n;
             const uint64_t P = part_size_dev(n, a.gnum, a.gden);
             const uint64_t total = d.keys ? 0 : d.offs[n];
+            auto slow = [&](uint64_t) { return !d.keys; };
             auto fetch = [&](uint32_t i, uint64_t sd) -> ulonglong2 {
                 uint64_t x, y;
-                if (d.keys) {
-                    key_digest(a, d, i, sd, x, y);
-                } else {
-                    const uint64_t o0 = d.offs[i], o1 = d.offs[i + 1];
-                    digest_str(d.bytes, o0, o1 - o0, total, fin(sd + kGamma), fin(sd + 2 * kGamma), x, y);
-                }
+                key_digest(a, d, i, sd, x, y);
+                return make_ulonglong2(x, y);
+            };
+            auto digest = [&](uint32_t i, uint64_t sd) -> ulonglong2 {
+                const uint64_t o0 = d.offs[i], o1 = d.offs[i + 1];
+                uint64_t x, y;
+                digest_str(d.bytes, o0, o1 - o0, total, fin(sd + kGamma), fin(sd + 2 * kGamma), x, y);
                 return make_ulonglong2(x, y);
             };
             auto locals = [&](ulonglong2 key, uint64_t) -> uint3 { return digest_locals(key.x, key.y, P); };
-            const LdsOutcome out = lds_build<kBlock, true, 4>((uint32_t)n, (uint32_t)P, d.seed, a.max_tries, fetch,
-                                                              locals, lds, nullptr, nullptr, d.codes, d.rank);
+            const LdsOutcome out = lds_build<kBlock, true, 4>((uint32_t)n, (uint32_t)P, d.seed, a.max_tries, slow, fetch,
+                                                              digest, locals, lds, nullptr, nullptr, d.codes, d.rank);
             left = out.status == kLdsTooDense;
             if (threadIdx.x == 0 && !left)
                 write_result(d.result, out.seed, out.tries, out.status, out.rounds);

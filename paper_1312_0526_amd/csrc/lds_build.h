@@ -71,12 +71,16 @@ __device__ __forceinline__ uint32_t queue_reserve(uint32_t* tail, bool want1, bo
 
 // Builds the MPHF of n keys with parts of P vertices (m = 3P at most kLdsMaxVertices) by all kBlock
 // threads of the workgroup.  fetch(i, sd) reads what key i's vertices under seed sd come from and
-// locals(key, sd) gives its three part-local vertices (kAhead reads are in flight at once).
+// locals(key, sd) gives its three part-local vertices; kAhead reads are in flight at once, unless
+// slow(sd), where digest(i, sd) takes fetch's place: kAhead copies of a string's hashing cost more
+// in instruction fetches than they hide (a served request of 3,638 strings took 269 us with four,
+// 208 with one).
 // lds: lds_build_bytes(m, kQueueLds) bytes, 16-byte aligned; gqueue: m entries in device memory,
 // used unless kQueueLds; gstart: n + 2 words in device memory, or null: then a peel of kLdsRounds
 // rounds or more is left to the general path too.
-template <int kBlock, bool kQueueLds, int kAhead, class Fetch, class Locals>
-__device__ LdsOutcome lds_build(uint32_t n, uint32_t P, uint64_t seed, uint32_t max_tries, Fetch fetch, Locals locals,
+template <int kBlock, bool kQueueLds, int kAhead, class Slow, class Fetch, class Digest, class Locals>
+__device__ LdsOutcome lds_build(uint32_t n, uint32_t P, uint64_t seed, uint32_t max_tries, Slow slow, Fetch fetch,
+                                Digest digest, Locals locals,
                                 uint8_t* lds, uint16_t* gqueue, uint32_t* gstart, uint64_t* codes, uint64_t* rank)
 {
     LdsBuildState& st = *reinterpret_cast<LdsBuildState*>(lds);
@@ -111,27 +115,33 @@ __device__ LdsOutcome lds_build(uint32_t n, uint32_t P, uint64_t seed, uint32_t 
             st.more[0] = 0;
         }
         __syncthreads();
-        for (uint32_t i0 = tid; i0 < n; i0 += kAhead * kBlock) {
-            decltype(fetch(0u, sd)) key[kAhead];
+        auto insert = [&](uint3 u) {
+            const uint32_t v1 = P + u.y, v2 = 2 * P + u.z;
+            const uint32_t s0 = 8 * (u.x & 3), s1 = 8 * (v1 & 3), s2 = 8 * (v2 & 3);
+            const uint32_t d0 = atomicAdd(&deg4[u.x >> 2], 1u << s0);
+            const uint32_t d1 = atomicAdd(&deg4[v1 >> 2], 1u << s1);
+            const uint32_t d2 = atomicAdd(&deg4[v2 >> 2], 1u << s2);
+            atomicXor(&word[u.x], u.y | u.z << 16);
+            atomicXor(&word[v1], u.z | u.x << 16);
+            atomicXor(&word[v2], u.x | u.y << 16);
+            if (max(d0 >> s0 & 255u, max(d1 >> s1 & 255u, d2 >> s2 & 255u)) >= kMaxLdsDegree)
+                st.err = 1;
+        };
+        if (slow(sd)) {
+#pragma unroll 1
+            for (uint32_t i = tid; i < n; i += kBlock)
+                insert(locals(digest(i, sd), sd));
+        } else {
+            for (uint32_t i0 = tid; i0 < n; i0 += kAhead * kBlock) {
+                decltype(fetch(0u, sd)) key[kAhead];
 #pragma unroll
-            for (uint32_t q = 0; q < kAhead; q++)
-                if (i0 + q * kBlock < n)
-                    key[q] = fetch(i0 + q * kBlock, sd);
+                for (uint32_t q = 0; q < kAhead; q++)
+                    if (i0 + q * kBlock < n)
+                        key[q] = fetch(i0 + q * kBlock, sd);
 #pragma unroll
-            for (uint32_t q = 0; q < kAhead; q++) {
-                if (i0 + q * kBlock < n) {
-                    const uint3 u = locals(key[q], sd);
-                    const uint32_t v1 = P + u.y, v2 = 2 * P + u.z;
-                    const uint32_t s0 = 8 * (u.x & 3), s1 = 8 * (v1 & 3), s2 = 8 * (v2 & 3);
-                    const uint32_t d0 = atomicAdd(&deg4[u.x >> 2], 1u << s0);
-                    const uint32_t d1 = atomicAdd(&deg4[v1 >> 2], 1u << s1);
-                    const uint32_t d2 = atomicAdd(&deg4[v2 >> 2], 1u << s2);
-                    atomicXor(&word[u.x], u.y | u.z << 16);
-                    atomicXor(&word[v1], u.z | u.x << 16);
-                    atomicXor(&word[v2], u.x | u.y << 16);
-                    if (max(d0 >> s0 & 255u, max(d1 >> s1 & 255u, d2 >> s2 & 255u)) >= kMaxLdsDegree)
-                        st.err = 1;
-                }
+                for (uint32_t q = 0; q < kAhead; q++)
+                    if (i0 + q * kBlock < n)
+                        insert(locals(key[q], sd));
             }
         }
         __syncthreads();

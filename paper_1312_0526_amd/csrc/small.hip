@@ -10,14 +10,15 @@ __global__ __launch_bounds__(kBlock) void k_small_build(SmallArgs a)
     __shared__ __align__(16) uint8_t s_lds[kBytes];
     const uint64_t total = a.keys ? 0 : a.offs[a.n];
     const uint64_t P = a.P;
-    // u64 keys as they are; strings as their digest, or as their hashed edge
-    auto fetch = [&](uint32_t i, uint64_t sd) -> ulonglong2 {
+    // u64 keys as they are; strings as their hashed edge, or as their digest
+    auto slow = [&](uint64_t sd) { return !a.keys && !(a.edges && sd == a.seed); };
+    auto fetch = [&](uint32_t i, uint64_t) -> ulonglong2 {
         if (a.keys)
             return make_ulonglong2(a.keys[i], 0);
-        if (a.edges && sd == a.seed) {
-            const uint32_t* t = a.edges + 3 * (uint64_t)i;
-            return make_ulonglong2(t[0] | (uint64_t)t[1] << 32, t[2]);
-        }
+        const uint32_t* t = a.edges + 3 * (uint64_t)i;
+        return make_ulonglong2(t[0] | (uint64_t)t[1] << 32, t[2]);
+    };
+    auto digest = [&](uint32_t i, uint64_t sd) -> ulonglong2 {
         const uint64_t o0 = a.offs[i], o1 = a.offs[i + 1];
         uint64_t x, y;
         digest_str(a.bytes, o0, o1 - o0, total, fin(sd + kGamma), fin(sd + 2 * kGamma), x, y);
@@ -32,8 +33,8 @@ __global__ __launch_bounds__(kBlock) void k_small_build(SmallArgs a)
         return make_uint3((uint32_t)range_reduce(fin(x + kGamma), P), (uint32_t)range_reduce(fin(x + 2 * kGamma), P),
                           (uint32_t)range_reduce(fin(y + 3 * kGamma), P));
     };
-    const LdsOutcome out = lds_build<kBlock, kQueueLds, 4>(a.n, a.P, a.seed, a.max_tries, fetch, locals, s_lds, a.queue,
-                                                           a.start, a.codes, a.rank);
+    const LdsOutcome out = lds_build<kBlock, kQueueLds, 4>(a.n, a.P, a.seed, a.max_tries, slow, fetch, digest, locals,
+                                                           s_lds, a.queue, a.start, a.codes, a.rank);
     if (threadIdx.x == 0)
         *a.out = out;
 }

@@ -140,3 +140,18 @@ def test_batched_codes_partly_in_lds(mx, o, block, vertices):
         assert status == oracle.OK and res[b]["status"] == 0
         assert np.array_equal(words(bb.bucket_codes(b)), want["words"]), b
         assert np.array_equal(words(bb.bucket_rank(b)), want["rank"]), b
+
+
+# the last strings of an array, where a read of whole words would pass its end
+@pytest.mark.parametrize("first", [0, 1, 2, 3])
+def test_strings_at_the_end_of_the_array(mx, o, first):
+    rng = np.random.default_rng(first)
+    for last in list(range(0, 40)) + [63, 64, 65, 100]:
+        lens = np.array([first + 5, 9, 31, 32, 33, 70, 36, last + 6], dtype=np.uint64)
+        offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
+        data = rng.integers(0, 256, int(offs[-1]), dtype=np.uint8)
+        status, want = o.mphf_build_str(data, offs, 1)
+        assert status == oracle.OK
+        got = mx.mphf_build_str(dev(data), dev(offs), seed=1)
+        assert got["tries"] == want["tries"]
+        assert np.array_equal(words(got["codes"]), want["words"])
