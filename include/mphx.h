@@ -605,7 +605,9 @@ MPHX_API int mphx_gen_str_bytes(uint8_t* bytes, const uint64_t* offs, uint64_t n
  *   "claim_lists" b in 0..32 (default 26): mphx_mphf_build_* with n >= 2^b keys claims the
  *                 edges of each layer after the first by appending (edge, position) lists
  *                 that are radix-partitioned by edge and resolved in LDS, instead of one
- *                 device atomic per claim, and reads one count back per round.  0 = never.
+ *                 device atomic per claim, and reads one count back per round; rounds of at
+ *                 most min(n / 128, 2^20) edges share a launch with atomic claims instead.
+ *                 0 = never.
  *                 The same codes either way; the workspace grows by 16 bytes per vertex, so
  *                 query mphx_mphf_workspace_bytes after setting it.
  *   "update_lists" p in 0..100 (default 16): in a claim-list build, a round whose claim count

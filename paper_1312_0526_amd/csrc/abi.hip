@@ -317,6 +317,19 @@ unsigned auto_grid(uint64_t work)
     return (unsigned)std::min<uint64_t>(std::max<uint64_t>(b, 64), 1024);
 }
 
+// Failures that a run's control block reports: round 0's checks, the round limit.
+int check_run_errors(const Ctrl& h, uint64_t n, uint64_t rcap, uint32_t r = 3)
+{
+    if (h.err & kErrBadEdge)
+        return fail(MPHX_EINVAL, "edge with a vertex id >= m or a repeated vertex");
+    // every degree field at most 255 and their total exactly r n: no field overflowed
+    if ((h.err & kErrDegree) || h.degsum != (uint64_t)r * n)
+        return fail(MPHX_ERANGE, "a vertex has degree above %u", MPHX_MAX_DEGREE);
+    if (h.err & kErrRounds)
+        return fail(MPHX_ERANGE, "more than %llu peeling rounds", (unsigned long long)rcap);
+    return MPHX_OK;
+}
+
 constexpr uint32_t kLaterBatch = 16;
 
 // Enqueue rounds in batches until a round finds an empty layer.  On return
@@ -366,11 +379,23 @@ constexpr int kListOverflow = 1000;  // internal: a round's records exceeded the
 // bucket (Section 4.2's sort-based round update), which leaves the next claims in
 // st.claims_tmp; a sparse round deletes with atomics and appends claims and cancels to
 // st.claims.
+//
+// Once a layer is small the rounds go on in one launch with atomic claims (launch_rounds), until a
+// layer is large again, which happens towards the end of a peel near the threshold.  A plateau round
+// of 490,000 edges at 2^27 keys takes 103 us there and 140 through the lists, a dozen launches and a
+// host read included; a round of 10^6 edges about the same; beyond, a workgroup's list spills (2x10^6
+// edges took 810 us and 540).  Whole builds of u64 keys, lists alone against both in turn: 22.0 and
+// 19.5 ms at 6.8x10^7, 37.9 and 35.7 at 2^27, 70.5 and 69.9 at 2.68x10^8; with 2^19 in place of 2^20: 36.8 and
+// 70.4.  n / 128 keeps the lists' rounds of a smaller run (option "claim_lists") where they belong.
+constexpr uint64_t kRunLayerMax = 1ull << 20;
 int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
 {
     const uint64_t upd = (uint64_t)g_opt.update_lists.load();
+    const uint64_t small = std::min<uint64_t>(st.n / 128, kRunLayerMax), large = small + small / 8;
     bool in_tmp = false;  // round r's claims sit in st.claims_tmp
+    bool states = false;  // st.state holds the unclaimed edges' states
     for (uint32_t r = 0;; r++) {
+        bool in_slot = true;  // where layer r's hinges are
         if (r > st.rcap)
             return fail(MPHX_ERANGE, "more than %llu peeling rounds", (unsigned long long)st.rcap);
         unsigned long long est = 0;
@@ -379,8 +404,36 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
             HIP_TRY(hipStreamSynchronize(s));
             if (est > st.lcap)
                 return kListOverflow;  // the list holds m records; no layer of a large random graph comes near
-            Timed t(PH_RESOLVE, s);
-            HIP_TRY(launch_claims_resolve(st, r, est, in_tmp, s));
+            {
+                Timed t(PH_RESOLVE, s);
+                HIP_TRY(launch_claims_resolve(st, r, est, in_tmp, s));
+            }
+            if (est <= small) {  // the claims bound the layer
+                if (!states) {
+                    HIP_TRY(launch_fill_u32(st.state, st.n, kUnclaimed, s));
+                    states = st.state != reinterpret_cast<uint32_t*>(st.claims_tmp);
+                }
+                HIP_TRY(launch_rounds_resume(st, r, s));
+                st.grid_cap = (unsigned)g_opt.grid.load();
+                for (;;) {
+                    {
+                        Timed t(PH_APPLY, s);
+                        HIP_TRY(launch_rounds(st, 3, false, large, s));
+                    }
+                    int rc = read_ctrl(st.ctrl, h, s);
+                    if (!rc) rc = check_run_errors(h, st.n, st.rcap);
+                    if (rc) return rc;
+                    if (h.nrounds != 0xFFFFFFFFu) {
+                        *peeled = h.peeled;
+                        return MPHX_OK;
+                    }
+                    HIP_TRY(launch_sync_zero(st, s));  // the claim counts too
+                    if (h.run_list > large) break;
+                }
+                r = h.run_r;
+                est = h.run_list;
+                in_slot = false;
+            }
         } else {
             HIP_TRY(hipMemcpyAsync(&est, st.lcount, sizeof est, hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
@@ -405,7 +458,7 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
         const bool updates = upd > 0 && 2 * est <= st.lcap && 200 * (unsigned __int128)est >= (unsigned __int128)upd * st.m;
         {
             Timed t(PH_APPLY, s);
-            HIP_TRY(launch_apply(st, r, true, updates ? ApplyMode::kUpdateList : ApplyMode::kClaimList, s));
+            HIP_TRY(launch_apply(st, r, in_slot, updates ? ApplyMode::kUpdateList : ApplyMode::kClaimList, s));
         }
         in_tmp = false;
         if (updates) {
@@ -430,19 +483,6 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
     return MPHX_OK;
 }
 
-// Failures that a run's control block reports: round 0's checks, the round limit.
-int check_run_errors(const Ctrl& h, uint64_t n, uint64_t rcap, uint32_t r = 3)
-{
-    if (h.err & kErrBadEdge)
-        return fail(MPHX_EINVAL, "edge with a vertex id >= m or a repeated vertex");
-    // every degree field at most 255 and their total exactly r n: no field overflowed
-    if ((h.err & kErrDegree) || h.degsum != (uint64_t)r * n)
-        return fail(MPHX_ERANGE, "a vertex has degree above %u", MPHX_MAX_DEGREE);
-    if (h.err & kErrRounds)
-        return fail(MPHX_ERANGE, "more than %llu peeling rounds", (unsigned long long)rcap);
-    return MPHX_OK;
-}
-
 // All rounds of a run of at most kRunMaxEdges edges whose layer 0 is enqueued, then finish()
 // (enqueued after every launch of rounds; it does nothing while the peel goes on).  One host
 // read unless the peel has more rounds than a launch takes.
@@ -453,7 +493,7 @@ int run_rounds_grid(PeelState& st, uint32_t r, bool generic_shift, Ctrl& h, hipS
     for (;;) {
         {
             Timed t(PH_APPLY, s);
-            HIP_TRY(launch_rounds(st, r, generic_shift, s));
+            HIP_TRY(launch_rounds(st, r, generic_shift, ~0ull, s));
         }
         HIP_TRY(finish());
         int rc = read_ctrl(st.ctrl, h, s);
@@ -1145,6 +1185,7 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
         if (!st.lists && !bins)
             HIP_TRY(launch_fill_u32(L.state, n, kUnclaimed, s));
         st.round0_updates = st.lists && g_opt.update_lists.load() > 0;
+        st.state = sf && st.lists ? reinterpret_cast<uint32_t*>(L.claims_tmp) : L.state;
         if (sf) {
             // the values in layer order: over the edge states with claim lists; over the idle
             // claim buffers when a try fell back to atomic claims; else their own array

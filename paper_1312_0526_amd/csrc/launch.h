@@ -141,10 +141,15 @@ hipError_t launch_apply(const PeelState& st, uint32_t r, bool hinge_in_slot, App
 // launches against one launch took 2450 and 1832 us at 10^7 keys, 5760 and 5743 at 3x10^7, 11574
 // and 14285 at 6x10^7, where the rounds are bound by the device atomics and many small
 // workgroups keep more of them in flight.
-constexpr uint64_t kRunMaxEdges = 1ull << 24;  // (27-bit counts in a barrier's payload)
+constexpr uint64_t kRunMaxEdges = 1ull << 24;
 size_t run_sync_bytes();
 hipError_t launch_run_init(const PeelState& st, uint64_t zero_words, hipStream_t s);
-hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, hipStream_t s);
+// A layer of more than limit edges ends the launch too, all of it in the slots (edge ids, hinges in
+// the states) and its size in lcount.
+hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, hipStream_t s);
+// Before launch_rounds on layer r of a claim-list run: the layer's states (all others unclaimed, in
+// st.state, by the caller), the run's place, zeroed barrier words.
+hipError_t launch_rounds_resume(const PeelState& st, uint32_t r, hipStream_t s);
 hipError_t launch_rounds_again(const PeelState& st, hipStream_t s);
 // All layers of a complete peel of nrounds rounds in one launch, any size; the MPHF's codes and
 // rank samples, or a static function's values u (over the records).  nrounds 0: enqueued behind

@@ -24,6 +24,8 @@ namespace mphx {
 
 constexpr uint32_t kRoundsBlock = 512;
 constexpr uint32_t kPrivate = 4096;          // edges of a workgroup's own list
+constexpr uint32_t kPrivateBits = 21;        // a barrier's payload: edges of private lists, then of the shared one
+static_assert(kPrivate * kGridMax < 1u << kPrivateBits && kPrivateBits + 32 <= 54, "both counts fit");
 // Every so many rounds all edges of the next layer go through the shared list, which deals them out
 // evenly: the private lists grow by descent, and without it one of 122 workgroups held 4 times its
 // share of a layer after 50 rounds at 10^6 keys.  The rounds took 397, 386, 385 and 412 us with a deal
@@ -75,10 +77,11 @@ struct RoundsArgs {
     uint32_t* state;
     uint3* slots;
     uint64_t* lstart;
-    const unsigned long long* lcount;
+    unsigned long long* lcount;
     Ctrl* ctrl;
     GridSync* sync;
     uint64_t n, P, rcap;
+    uint64_t limit;  // a layer beyond it ends the launch
     const uint32_t* vin;  // static functions: see PeelState
     uint32_t* vout;
 };
@@ -144,6 +147,14 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
         if (lo == hi)
             break;
         if (done == kRoundsPerLaunch) {
+            more = true;
+            break;
+        }
+        if (hi - lo > a.limit && done) {
+            // the private lists join the shared one; the hinges stay in the states
+            for (uint32_t i = tid; i < pc; i += kRoundsBlock)
+                a.slots[pbase + i].x = s_list[cur][i];
+            glist = hi - lo;
             more = true;
             break;
         }
@@ -250,7 +261,7 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
             [&]() -> uint64_t {
                 const uint32_t k = *count, p = min(k, cap);
                 s_next[cur] = 0;
-                return (uint64_t)p | (uint64_t)(k - p) << 27;
+                return (uint64_t)p | (uint64_t)(k - p) << kPrivateBits;
             },
             [&] {
                 if constexpr (kTri) {
@@ -274,8 +285,8 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
             },
             [&] { s_off = off; });
         lo = hi;
-        ptot = total & ((1ull << 27) - 1);
-        glist = total >> 27;
+        ptot = total & ((1ull << kPrivateBits) - 1);
+        glist = total >> kPrivateBits;
         pc = pnext;
         pbase = lo + glist + (s_off - psum);
         const uint64_t passed = psum + ptot;
@@ -286,11 +297,12 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
     }
     if (lead) {
         if (more) {
+            a.lcount[r] = glist;
             c->run_lo = lo;
             c->run_list = glist;
             c->run_r = r;
         } else if (r < a.rcap) {
-            c->nrounds = r;
+            c->nrounds = min(c->nrounds, r);  // a claim-list round may have been the first empty one
             c->peeled = lo;
         }
     }
@@ -532,11 +544,39 @@ hipError_t launch_run_init(const PeelState& st, uint64_t zero_words, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, hipStream_t s)
+hipError_t launch_sync_zero(const PeelState& st, hipStream_t s) { return launch_zero(st.sync, run_sync_bytes(), s); }
+
+// The edge states and the run's place, for rounds that go on from layer r of a claim-list run (its
+// slots hold edge and hinge).
+__global__ __launch_bounds__(256) void k_rounds_resume(const uint3* __restrict__ slots,
+                                                       const uint64_t* __restrict__ lstart,
+                                                       const unsigned long long* __restrict__ lcount,
+                                                       uint32_t* __restrict__ state, Ctrl* ctrl, uint32_t r)
 {
-    if (st.n > kRunMaxEdges) return hipErrorInvalidValue;
+    const uint64_t lo = lstart[r], count = lcount[r], stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) {
+        const uint3 t = slots[lo + i];
+        state[t.x] = r << 2 | (t.y & 3u);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctrl->run_lo = lo;
+        ctrl->run_list = count;
+        ctrl->run_r = r;
+    }
+}
+
+hipError_t launch_rounds_resume(const PeelState& st, uint32_t r, hipStream_t s)
+{
+    hipError_t e = launch_sync_zero(st, s);
+    if (e != hipSuccess) return e;
+    k_rounds_resume<<<1024, 256, 0, s>>>(st.slots, st.lstart, st.lcount, st.state, st.ctrl, r);
+    return hipGetLastError();
+}
+
+hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, hipStream_t s)
+{
     const RoundsArgs a{st.rec, st.edges, st.state, st.slots, st.lstart, st.lcount, st.ctrl, st.sync,
-                       st.n,   st.P,     st.rcap,  st.vin,   st.vout};
+                       st.n,   st.P,     st.rcap,  limit,    st.vin,    st.vout};
     const unsigned g = run_grid(st);
     if (st.tripartite) {
         if (r != 3 || generic_shift) return hipErrorInvalidValue;
@@ -573,7 +613,6 @@ hipError_t launch_copy_ctrl(const Ctrl* ctrl, Ctrl* out, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_sync_zero(const PeelState& st, hipStream_t s) { return launch_zero(st.sync, run_sync_bytes(), s); }
 hipError_t launch_rounds_again(const PeelState& st, hipStream_t s) { return launch_sync_zero(st, s); }
 
 hipError_t launch_mphf_finish(const PeelState& st, uint32_t nrounds, uint64_t* codes, uint64_t* rank, uint32_t* bcount,

@@ -113,3 +113,29 @@ def test_builds_side_by_side(mx, n):
     for t in threads:
         t.join()
     assert not wrong
+
+
+# claim-list rounds hand small layers over to one launch and take large ones back
+@pytest.mark.parametrize("n,update_lists", [(100_003, 16), (1_000_001, 16), (1_000_001, 0), (3_000_000, 1)])
+def test_lists_and_one_launch_in_turn(mx, o, n, update_lists):
+    keys = workloads.u64_keys(n, gen_seed=n)
+    vals = (np.arange(n) % 251).astype(np.uint32)
+    status, want = o.mphf_build_u64(keys, 4)
+    assert status == oracle.OK
+    status, sf = o.sf_build_u64(keys, vals, 251, 4)
+    assert status == oracle.OK
+    old = mx.get_option("claim_lists"), mx.get_option("update_lists")
+    other = mx.mphf_build_u64(dev(keys), seed=4)
+    mx.set_option("claim_lists", 1)
+    mx.set_option("update_lists", update_lists)
+    try:
+        got = mx.mphf_build_u64(dev(keys), seed=4)
+        fn = mx.sf_build_u64(dev(keys), dev(vals), 251, seed=4)
+    finally:
+        mx.set_option("claim_lists", old[0])
+        mx.set_option("update_lists", old[1])
+    assert [got[k] for k in ("tries", "n_rounds", "claims", "layer0")] == \
+        [other[k] for k in ("tries", "n_rounds", "claims", "layer0")]
+    assert np.array_equal(words(got["codes"]), want["words"])
+    assert np.array_equal(words(got["rank"]), want["rank"])
+    assert np.array_equal(words(fn["words"]), sf["words"])
