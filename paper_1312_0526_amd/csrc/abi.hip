@@ -183,7 +183,7 @@ void layout_peel(Carve& c, uint64_t n, uint64_t m, PeelLayout& L)
     L.slots = c.take<uint3>(n);
     L.state = c.take<uint32_t>(n);
     L.ids = reinterpret_cast<uint32_t*>(L.slots);  // sort scratch once the peel is over
-    uint64_t hist_entries = 256 * sort_tiles(n);
+    uint64_t hist_entries = 256 * sort_tiles_max(n);
     L.tilehist = c.take<uint32_t>(hist_entries);
     L.scan_bytes = scan_scratch_bytes(hist_entries);
     L.scan = c.take<uint8_t>(L.scan_bytes);

@@ -162,7 +162,8 @@ hipError_t launch_mphf_finish(const PeelState& st, uint32_t nrounds, uint64_t* c
 hipError_t launch_sf_solve(const PeelState& st, uint32_t nrounds, uint64_t sigma, uint32_t b, hipStream_t s);
 hipError_t launch_peel_finalize(const uint32_t* state, uint64_t n, uint32_t* round, uint8_t* core_mask,
                                 uint8_t* hinge, hipStream_t s);
-uint64_t sort_tiles(uint64_t n);
+// tiles of launch_order_sort for at most n ids (256 histogram words each)
+uint64_t sort_tiles_max(uint64_t n);
 hipError_t launch_order_sort(const uint32_t* round, uint64_t n, uint32_t nrounds, uint32_t* order,
                              uint32_t* scratch_ids, uint32_t* tilehist, void* scan_scratch, size_t scan_bytes,
                              hipStream_t s);
