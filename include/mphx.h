@@ -606,7 +606,8 @@ MPHX_API int mphx_gen_str_bytes(uint8_t* bytes, const uint64_t* offs, uint64_t n
  *                 edges of each layer after the first by appending (edge, position) lists
  *                 that are radix-partitioned by edge and resolved in LDS, instead of one
  *                 device atomic per claim, and reads one count back per round; rounds of at
- *                 most min(n / 128, 2^20) edges share a launch with atomic claims instead.
+ *                 most min(n / 128, 2^20) edges share a launch with atomic claims instead
+ *                 (n up to 2^28).
  *                 0 = never.
  *                 The same codes either way; the workspace grows by 16 bytes per vertex, so
  *                 query mphx_mphf_workspace_bytes after setting it.

@@ -386,12 +386,15 @@ constexpr int kListOverflow = 1000;  // internal: a round's records exceeded the
 // host read included; a round of 10^6 edges about the same; beyond, a workgroup's list spills (2x10^6
 // edges took 810 us and 540).  Whole builds of u64 keys, lists alone against both in turn: 22.0 and
 // 19.5 ms at 6.8x10^7, 37.9 and 35.7 at 2^27, 70.5 and 69.9 at 2.68x10^8; with 2^19 in place of 2^20: 36.8 and
-// 70.4.  n / 128 keeps the lists' rounds of a smaller run (option "claim_lists") where they belong.
-constexpr uint64_t kRunLayerMax = 1ull << 20;
+// 70.4.  n / 128 keeps the lists' rounds of a smaller run (option "claim_lists") where they belong.  Above
+// 2^28 keys even the smallest plateau round is larger, and the states' fill would be for the last two
+// or three rounds alone.
+constexpr uint64_t kRunLayerMax = 1ull << 20, kRunStatesMax = 1ull << 28;
 int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
 {
     const uint64_t upd = (uint64_t)g_opt.update_lists.load();
-    const uint64_t small = std::min<uint64_t>(st.n / 128, kRunLayerMax), large = small + small / 8;
+    const uint64_t small = st.n <= kRunStatesMax ? std::min<uint64_t>(st.n / 128, kRunLayerMax) : 0;
+    const uint64_t large = small + small / 8;
     bool in_tmp = false;  // round r's claims sit in st.claims_tmp
     bool states = false;  // st.state holds the unclaimed edges' states
     for (uint32_t r = 0;; r++) {
@@ -408,7 +411,7 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
                 Timed t(PH_RESOLVE, s);
                 HIP_TRY(launch_claims_resolve(st, r, est, in_tmp, s));
             }
-            if (est <= small) {  // the claims bound the layer
+            if (small && est <= small) {  // the claims bound the layer
                 if (!states) {
                     HIP_TRY(launch_fill_u32(st.state, st.n, kUnclaimed, s));
                     states = st.state != reinterpret_cast<uint32_t*>(st.claims_tmp);
@@ -959,8 +962,8 @@ struct SfArgs {
     uint64_t* vals = nullptr;
 };
 
-// String keys beyond this many are hashed by a launch of their own, whose workgroups share them;
-// one workgroup hashes fewer at once.
+// String keys beyond this many are hashed by a launch of their own (6 us), whose workgroups share them;
+// one workgroup hashes fewer at once (two keys a thread).
 constexpr uint64_t kSmallStrHash = 2048;
 constexpr uint32_t kFirstTryAgain = 0xFFFFFFFFu;
 

@@ -20,6 +20,10 @@
 // round carries no mark yet, or the next round's; one that fell 2 -> 1 -> 0 has degree 0.
 // Same rounds and hinges as the other paths, hence the same codes.
 //
+// Measured: 0.95 us a round and 0.35 a layer whatever the block size (256 to 1024 threads): some 170
+// instructions and 7 LDS accesses of one wave in a row.  A bucket of 16,384 keys takes 137 us; as 32-bit
+// records and edge states with the slots in device memory it took 200.
+//
 // A degree above 63 (mean 2.4) leaves the build to the caller's general path.
 #pragma once
 
