@@ -1107,13 +1107,19 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
         if (rc || t0 == 0) return rc;
         if (t0 == kFirstTryAgain) t0 = 0;
     }
-    if (sf) {  // every value below sigma
+    // every value below sigma: checked first, or by the first try where that reads the host back only
+    // once (20 us of 1040 at 2x10^6 keys)
+    const bool check_later = !lists && n <= kRunMaxEdges;
+    auto bad_value = [&] {
+        return fail(MPHX_EINVAL, "a value is not below sigma = %llu", (unsigned long long)sf->sigma);
+    };
+    if (sf && !check_later) {
         HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
         HIP_TRY(launch_sf_check(sf->values, n, sf->sigma, L.ctrl, s));
         Ctrl hc;
         int rc = read_ctrl(L.ctrl, hc, s);
         if (rc) return rc;
-        if (hc.err & kErrValue) return fail(MPHX_EINVAL, "a value is not below sigma = %llu", (unsigned long long)sf->sigma);
+        if (hc.err & kErrValue) return bad_value();
     }
 
     PeelState st{};
@@ -1156,6 +1162,8 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
         grid_run = !st.lists && n <= kRunMaxEdges;
         if (grid_run) {
             HIP_TRY(launch_run_init(st, bins ? bins_zero_words(m, bins) : 1, s));
+            if (sf && check_later && t == 0)
+                HIP_TRY(launch_sf_check(sf->values, n, sf->sigma, L.ctrl, s));
         } else {
             HIP_TRY(launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
             HIP_TRY(launch_zero(L.ccount, 2 * (st.rcap + 2) * sizeof(unsigned long long), s));
@@ -1204,6 +1212,7 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
         if (grid_run) {
             // the rest of the build is enqueued with the rounds; it waits for a complete peel
             rc = run_rounds_grid(st, 3, false, h, s, [&] { return solve(0); });
+            if (h.err & kErrValue) return bad_value();
             f0 = h.f0;
             peeled = h.peeled;
             if (rc == MPHX_ERANGE && !(h.err & kErrRounds) && info) { info->tries = t + 1; info->seed_used = sd; }
