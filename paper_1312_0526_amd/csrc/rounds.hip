@@ -318,9 +318,13 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
 // The layers of a complete peel, last first, with a barrier after each: load(i) reads slot i, which
 // nobody changes, and solve(item) solves it; a thread's first slot of the next layer is read while
 // the group waits.  The layers at the end of a peel hold few edges: member 0 alone goes through
-// those at the top that one pass of its threads covers, with barriers of its own.
+// those at the top that one pass of its threads covers, with barriers of its own; with kHop through any
+// two such layers in a row, which the plateau of a small peel consists of.  Builds of u64 keys took 530 us
+// without and 478 with at 3x10^4, 467 and 437 at 4.5x10^4, 462 and 448 at 6x10^4, 492 and 490 at 10^5; at 10^6, where
+// no layer but the top ones is that small, the test itself costs 10 us.
 constexpr uint32_t kLayerChunk = 1024;
-template <class Item, class Load, class Solve>
+constexpr uint64_t kHopMax = 100'000;  // keys
+template <bool kHop, class Item, class Load, class Solve>
 __device__ __forceinline__ void solve_layers(Grid& g, const uint64_t* __restrict__ lstart, uint32_t nrounds,
                                              uint64_t* s_ls, uint64_t* s_total, Load load, Solve solve)
 {
@@ -338,7 +342,11 @@ __device__ __forceinline__ void solve_layers(Grid& g, const uint64_t* __restrict
         for (uint32_t k = top - base; k-- > 0;) {
             const uint64_t lo = s_ls[k], hi = s_ls[k + 1];
             const uint64_t below = k ? s_ls[k - 1] : lo;  // the next layer is [below, lo)
-            if (solo && hi - lo <= kRoundsBlock) {
+            if (hi - lo <= kRoundsBlock && (solo || (kHop && k && lo - below <= kRoundsBlock))) {
+                if (kHop && !solo) {
+                    solo = true;
+                    have = false;  // what was read ahead was the group's share
+                }
                 if (g.rank == 0) {
                     if (lo + tid < hi)
                         solve(have ? ahead : load(lo + tid));
@@ -383,6 +391,7 @@ __device__ __forceinline__ void zero_shared(Grid& g, uint64_t* p, uint64_t words
 // The whole rest of an MPHF build whose peel is complete: the codes (one byte per vertex, over
 // the records), layer by layer; the packed codes and rank samples, each member's share of the
 // vertices after a prefix over the members.  Does nothing after an incomplete peel.
+template <bool kHop>
 __global__ __launch_bounds__(kRoundsBlock) void k_mphf_finish(const uint3* __restrict__ slots,
                                                               const uint64_t* __restrict__ lstart, const Ctrl* ctrl,
                                                               GridSync* sync, uint32_t nrounds, uint64_t n, uint64_t m,
@@ -402,7 +411,7 @@ __global__ __launch_bounds__(kRoundsBlock) void k_mphf_finish(const uint3* __res
     uint8_t* const code8 = reinterpret_cast<uint8_t*>(code_words);
     zero_shared(g, code_words, (m + 7) / 8);  // 8m bytes of records hold it
     grid_barrier(g, &s_total);
-    solve_layers<uint3>(g, lstart, nrounds, s_ls, &s_total, [&](uint64_t i) { return slots[i]; }, [&](uint3 t) {
+    solve_layers<kHop, uint3>(g, lstart, nrounds, s_ls, &s_total, [&](uint64_t i) { return slots[i]; }, [&](uint3 t) {
         const uint32_t k = part_of(t.x, P);
         const uint32_t ca = ag_load(code8 + t.y), cb = ag_load(code8 + t.z);
         const uint32_t x = (k + 6 - (ca == 3 ? 0u : ca) - (cb == 3 ? 0u : cb)) % 3;
@@ -490,7 +499,7 @@ __global__ __launch_bounds__(kRoundsBlock) void k_mphf_finish(const uint3* __res
 
 // The values u of a static function whose peel is complete (zero off the hinges), as
 // k_sf_assign_round solves them.  Does nothing after an incomplete peel.
-template <typename T>
+template <typename T, bool kHop>
 __global__ __launch_bounds__(kRoundsBlock) void k_sf_solve(const uint3* __restrict__ slots,
                                                            const uint32_t* __restrict__ vals,
                                                            const uint64_t* __restrict__ lstart, const Ctrl* ctrl,
@@ -511,7 +520,7 @@ __global__ __launch_bounds__(kRoundsBlock) void k_sf_solve(const uint3* __restri
     zero_shared(g, u_words, (m * sizeof(T) + 7) / 8);
     grid_barrier(g, &s_total);
     auto load = [&](uint64_t i) { return make_uint4(slots[i].x, slots[i].y, slots[i].z, vals[i]); };
-    solve_layers<uint4>(g, lstart, nrounds, s_ls, &s_total, load, [&](uint4 t) {
+    solve_layers<kHop, uint4>(g, lstart, nrounds, s_ls, &s_total, load, [&](uint4 t) {
         uint64_t x = (uint64_t)t.w + 2 * sigma - ag_load(u + t.y) - ag_load(u + t.z);
         x = x >= sigma ? x - sigma : x;
         x = x >= sigma ? x - sigma : x;
@@ -618,17 +627,18 @@ hipError_t launch_rounds_again(const PeelState& st, hipStream_t s) { return laun
 hipError_t launch_mphf_finish(const PeelState& st, uint32_t nrounds, uint64_t* codes, uint64_t* rank, uint32_t* bcount,
                               hipStream_t s)
 {
-    k_mphf_finish<<<run_grid(st), kRoundsBlock, 0, s>>>(st.slots, st.lstart, st.ctrl, st.sync + 1, nrounds, st.n, st.m,
-                                                        st.P, st.rec, codes, rank, bcount);
+    auto* const finish = st.n <= kHopMax ? k_mphf_finish<true> : k_mphf_finish<false>;
+    finish<<<run_grid(st), kRoundsBlock, 0, s>>>(st.slots, st.lstart, st.ctrl, st.sync + 1, nrounds, st.n, st.m, st.P,
+                                                 st.rec, codes, rank, bcount);
     return hipGetLastError();
 }
 
 hipError_t launch_sf_solve(const PeelState& st, uint32_t nrounds, uint64_t sigma, uint32_t b, hipStream_t s)
 {
     const unsigned g = run_grid(st);
-#define MPHX_SOLVE(T) \
-    k_sf_solve<T><<<g, kRoundsBlock, 0, s>>>(st.slots, st.vout, st.lstart, st.ctrl, st.sync + 1, nrounds, st.n, st.m, \
-                                            sigma, st.rec)
+#define MPHX_SOLVE(T)                                                                                               \
+    (st.n <= kHopMax ? k_sf_solve<T, true> : k_sf_solve<T, false>)<<<g, kRoundsBlock, 0, s>>>(                      \
+        st.slots, st.vout, st.lstart, st.ctrl, st.sync + 1, nrounds, st.n, st.m, sigma, st.rec)
     switch (sf_elem_bytes(b)) {
     case 1: MPHX_SOLVE(uint8_t); break;
     case 2: MPHX_SOLVE(uint16_t); break;
