@@ -372,9 +372,10 @@ __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restr
     __shared__ ulonglong2 s_digest[kQuadKeys];
     const uint32_t tid = threadIdx.x, wlane = tid & (kWave - 1), lane = tid & 3;
     const uint64_t first = (uint64_t)blockIdx.x * kQuadKeys, i = first + tid / 4;
-    const uint64_t total = offs[n];
+    // the batch's keys are bytes [origin, total), a slice of a larger array perhaps: nothing outside is read
+    const uint64_t origin = offs[0], total = offs[n];
     const uint64_t sa = fin(seed + kGamma), sb = fin(seed + 2 * kGamma);
-    uint64_t o0 = 0, len = 0;
+    uint64_t o0 = origin, len = 0;
     if (i < n) {
         o0 = offs[i];
         len = offs[i + 1] - o0;
@@ -385,11 +386,11 @@ __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restr
         uint64_t w[4];
 #pragma unroll
         for (uint32_t u = 0; u < 4; u++) {
-            const uint64_t k = j + u * step, p = 8 * k < size ? at + 8 * k : 0ull;
-            // eight bytes that end inside the array
+            const uint64_t k = j + u * step, p = 8 * k < size ? at + 8 * k : at;
+            // eight bytes that end inside the array, and begin there: it has at least eight
             const uint64_t q = min(p, total - 8);
             __builtin_memcpy(&w[u], bytes + q, 8);
-            w[u] >>= 8 * (p - q);
+            w[u] >>= 8 * (p - q) & 63;  // an empty key may start at the array's end
         }
 #pragma unroll
         for (uint32_t u = 0; u < 4; u++) {
@@ -410,7 +411,7 @@ __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restr
             B += __shfl_xor(B, d, kWave);
         }
     };
-    if (total >= 8) {
+    if (total - origin >= 8) {
         const uint64_t near = min<uint64_t>(len, 8 * kQuadNear);
         for (uint64_t j = lane; 8 * j < near; j += 16)
             add(o0, near, j, 4);
