@@ -8,7 +8,9 @@
  *  - Pointers marked (dev) are device pointers on the current HIP device; (host) are host
  *    pointers.  The caller allocates and owns every buffer, including the workspace; the
  *    library never frees caller memory and allocates no device memory in these calls (the
- *    server API is the exception: it owns a pool sized by its budget).
+ *    server API is the exception: it owns a pool sized by its budget).  The first build or peel
+ *    of a process takes 16 KiB of pinned host memory, kept until the process ends, through which
+ *    results are read back; where none is to be had they are copied (some 10 us more per read).
  *  - `stream` is a hipStream_t passed as void*; all device work is enqueued on it.  Calls
  *    that return data-dependent results (status, info) synchronise that stream once or a
  *    few times before returning; the others only enqueue.
@@ -162,7 +164,8 @@ MPHX_API int mphx_mphf_build_str(const uint8_t* bytes, const uint64_t* offs, uin
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): mphx_mphf_build_u64 without the ws argument.  Its
  * workspace is a device array of 128 MiB (134,217,728 bytes) that the library
- * holds on every device it runs on until the process ends; the call allocates nothing.  It
+ * holds on every device it runs on until the process ends; the call allocates nothing (nor the
+ * pinned host memory of other builds: it uses that where a build has taken it before).  It
  * takes keys with a workspace up to that size (at gamma = 1.23, n <= 1,917,869 u64 keys) and
  * returns MPHX_ENOMEM, with a message, beyond it.  Arguments, outputs and results are those of
  * mphx_mphf_build_u64 (the same codes, rank and info).  Every call on a device shares that

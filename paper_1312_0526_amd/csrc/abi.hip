@@ -239,16 +239,22 @@ void layout_mphf(Carve& c, uint64_t n, uint64_t m, bool lists, MphfLayout& L, bo
 
 bool aligned256(const void* p) { return ((uintptr_t)p & 255) == 0; }
 
+thread_local bool t_may_allocate = true;  // the call under way may take host memory for the library
+struct AllocateNothing {
+    const bool was = t_may_allocate;
+    AllocateNothing() { t_may_allocate = false; }
+    ~AllocateNothing() { t_may_allocate = was; }
+};
+
 // Pinned words that kernels report through: writing one costs a build less than a copy back does
 // (about 10 us at 10^3 keys).  64 slots, taken for the time of a read and given back; with none
-// left, or no pinned memory, the caller copies instead.
+// left, no pinned memory, or none yet in a call that allocates nothing, the caller copies instead.
 class HostSlot {
     static constexpr int kSlots = 64;
     struct Pool {
         std::mutex mu;
         uint64_t used = 0;
         uint8_t* base = nullptr;
-        bool tried = false;
     };
     static Pool& pool()
     {
@@ -263,13 +269,16 @@ public:
     {
         Pool& p = pool();
         std::lock_guard<std::mutex> lk(p.mu);
-        if (!p.tried) {
-            p.tried = true;
+        if (!p.base && t_may_allocate) {
+            // other threads' captures are no business of this allocation, nor the other way round
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
             void* q = nullptr;
             if (hipHostMalloc(&q, kSlots * kBytes, hipHostMallocPortable) == hipSuccess)
                 p.base = (uint8_t*)q;
             else
-                (void)hipGetLastError();
+                (void)hipGetLastError();  // the next call tries again
+            if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
         }
         if (!p.base || !~p.used) return;
         i_ = __builtin_ctzll(~p.used);
@@ -1359,6 +1368,7 @@ int mphx_mphf_build_u64_static(const uint64_t* keys, uint64_t n, uint64_t seed, 
     if (need > kStaticScratchBytes)
         return fail(MPHX_ENOMEM, "%llu keys need %zu bytes of workspace; the allocation-free build has %zu",
                     (unsigned long long)n, need, kStaticScratchBytes);
+    const AllocateNothing scope;
     void* ws = nullptr;
     int rc = static_scratch(&ws);
     if (rc) return rc;
