@@ -658,6 +658,11 @@ MPHX_API int mphx_gen_str_bytes(uint8_t* bytes, const uint64_t* offs, uint64_t n
  *                 most m, the buffers' size).  A round with more claims, or a round 0 with
  *                 more deletes, makes the try start again with atomic claims (the same codes
  *                 either way); a small value exercises that fallback.
+ *   "group_wait"  0..1000 (default 20): microseconds that the first workgroup of a launch which holds
+ *                 all rounds, or all layers of the assignment, waits for the rest of the grid
+ *                 before the work begins (0: it begins alone).  Workgroups that find room later
+ *                 join in at the next barrier.  The same outputs either way.
+ *   "group_joins" (read; set only to 0 to reset) workgroups that joined so, over the process.
  *   "list_fallbacks" (read; set only to 0 to reset) tries redone with atomic claims after
  *                 a list overflowed, over the process.
  * Returns MPHX_EINVAL for an unknown key or value.

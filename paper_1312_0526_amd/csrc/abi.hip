@@ -40,6 +40,9 @@ struct Options {
     std::atomic<int> hem_block{1024};  // batched-kernel workgroup size for the HEM split's buckets
     std::atomic<int> hem_grid{0};      // its persistent grid (0 = one workgroup per compute unit)
     std::atomic<int64_t> list_cap{0};  // records a claim-list round may hold (0 = m, the buffers' size)
+    std::atomic<int> group_wait{20};   // microseconds that a group waits for its whole grid before it
+                                       // begins; workgroups that start later join it
+    std::atomic<int64_t> group_joins{0};     // workgroups that did so
     std::atomic<int64_t> list_fallbacks{0};  // tries redone with atomic claims after a list overflowed
     std::atomic<int> batch_lds{1};     // 1 = batched buckets that fit run entirely in LDS
     std::atomic<int> batch_sort_deletes{4};  // sorted deletes for layers with 2 * layer * this >= m
@@ -326,6 +329,8 @@ unsigned auto_grid(uint64_t work)
     return (unsigned)std::min<uint64_t>(std::max<uint64_t>(b, 64), 1024);
 }
 
+uint32_t group_wait_ticks() { return 100u * (uint32_t)g_opt.group_wait.load(); }
+
 // Failures that a run's control block reports: round 0's checks, the round limit.
 int check_run_errors(const Ctrl& h, uint64_t n, uint64_t rcap, uint32_t r = 3)
 {
@@ -404,6 +409,7 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
     const uint64_t upd = (uint64_t)g_opt.update_lists.load();
     const uint64_t small = st.n <= kRunStatesMax ? std::min<uint64_t>(st.n / 128, kRunLayerMax) : 0;
     const uint64_t large = small + small / 8;
+    uint32_t joined = 0;
     bool in_tmp = false;  // round r's claims sit in st.claims_tmp
     bool states = false;  // st.state holds the unclaimed edges' states
     for (uint32_t r = 0;; r++) {
@@ -427,20 +433,25 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
                 }
                 HIP_TRY(launch_rounds_resume(st, r, s));
                 st.grid_cap = (unsigned)g_opt.grid.load();
-                for (;;) {
+                bool grow = false;
+                for (uint32_t from = r;;) {
                     {
                         Timed t(PH_APPLY, s);
-                        HIP_TRY(launch_rounds(st, 3, false, large, s));
+                        HIP_TRY(launch_rounds(st, 3, false, large, grow, s));
                     }
                     int rc = read_ctrl(st.ctrl, h, s);
                     if (!rc) rc = check_run_errors(h, st.n, st.rcap);
                     if (rc) return rc;
+                    g_opt.group_joins += h.joined - joined;
+                    joined = h.joined;
+                    grow = h.run_r == from;
+                    from = h.run_r;
                     if (h.nrounds != 0xFFFFFFFFu) {
                         *peeled = h.peeled;
                         return MPHX_OK;
                     }
                     HIP_TRY(launch_sync_zero(st, s));  // the claim counts too
-                    if (h.run_list > large) break;
+                    if (!grow && h.run_list > large) break;
                 }
                 r = h.run_r;
                 est = h.run_list;
@@ -502,16 +513,22 @@ template <class Finish>
 int run_rounds_grid(PeelState& st, uint32_t r, bool generic_shift, Ctrl& h, hipStream_t s, Finish finish)
 {
     st.grid_cap = (unsigned)g_opt.grid.load();
+    uint32_t joined = 0, from = 0;
+    bool grow = false;
     for (;;) {
         {
             Timed t(PH_APPLY, s);
-            HIP_TRY(launch_rounds(st, r, generic_shift, ~0ull, s));
+            HIP_TRY(launch_rounds(st, r, generic_shift, ~0ull, grow, s));
         }
         HIP_TRY(finish());
         int rc = read_ctrl(st.ctrl, h, s);
         if (rc) return rc;
+        g_opt.group_joins += h.joined - joined;
+        joined = h.joined;
         rc = check_run_errors(h, st.n, st.rcap, r);
         if (rc || h.nrounds != 0xFFFFFFFFu) return rc;
+        grow = h.run_r == from;  // no round was made: the device is busy
+        from = h.run_r;
         HIP_TRY(launch_rounds_again(st, s));
     }
 }
@@ -612,6 +629,12 @@ int mphx_set_option(const char* key, int64_t value)
     } else if (!strcmp(key, "list_cap")) {
         if (value < 0) return fail(MPHX_EINVAL, "list_cap must be >= 0");
         g_opt.list_cap = value;
+    } else if (!strcmp(key, "group_wait")) {
+        if (value < 0 || value > 1000) return fail(MPHX_EINVAL, "group_wait must be in 0..1000");
+        g_opt.group_wait = (int)value;
+    } else if (!strcmp(key, "group_joins")) {
+        if (value != 0) return fail(MPHX_EINVAL, "group_joins can only be reset to 0");
+        g_opt.group_joins = 0;
     } else if (!strcmp(key, "list_fallbacks")) {
         if (value != 0) return fail(MPHX_EINVAL, "list_fallbacks can only be reset to 0");
         g_opt.list_fallbacks = 0;
@@ -637,6 +660,8 @@ int64_t mphx_get_option(const char* key)
     if (!strcmp(key, "batch_claim_lists")) return g_opt.batch_claim_lists;
     if (!strcmp(key, "batch_clock")) return g_opt.batch_clock;
     if (!strcmp(key, "list_cap")) return g_opt.list_cap;
+    if (!strcmp(key, "group_wait")) return g_opt.group_wait;
+    if (!strcmp(key, "group_joins")) return g_opt.group_joins;
     if (!strcmp(key, "list_fallbacks")) return g_opt.list_fallbacks;
     fail(MPHX_EINVAL, "unknown option '%s'", key);
     return MPHX_EINVAL;
@@ -711,6 +736,7 @@ int mphx_peel(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t* order, ui
     st.lcount = L.lcount;
     st.ctrl = L.ctrl;
     st.sync = L.sync;
+    st.wait = group_wait_ticks();
     st.rcap = round_cap(n);
 
     const bool grid_run = n <= kRunMaxEdges;
@@ -803,6 +829,7 @@ int mphx_peel_r(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t r, uint3
     st.lcount = L.lcount;
     st.ctrl = L.ctrl;
     st.sync = L.sync;
+    st.wait = group_wait_ticks();
     st.rcap = round_cap(n);
 
     HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
@@ -1040,6 +1067,15 @@ int small_build(const KeySrc& k, uint64_t n, uint64_t seed, uint64_t P, uint32_t
 // 49.5 and 50.8 at 7x10^8 (861 MB), 76.9 and 74.7 at 10^9.
 constexpr uint64_t kSolveGridMaxBytes = 1ull << 30;
 
+int pack_codes_and_rank(const PeelState& st, const MphfLayout& L, uint64_t* codes, uint64_t* rank, hipStream_t s)
+{
+    Timed tm(PH_RANK, s);
+    HIP_TRY(launch_pack_count(reinterpret_cast<uint8_t*>(L.rec), st.m, codes, L.bcount, s));
+    const uint64_t nblocks = (st.m + 511) / 512;
+    HIP_TRY(launch_scan_u32_to_u64(L.bcount, nblocks, rank, nblocks, L.scan, L.scan_bytes, s));
+    return MPHX_OK;
+}
+
 // Assignment in reverse round order, a launch per layer; an MPHF's codes and rank samples too.
 int solve_by_layer(const PeelState& st, const MphfLayout& L, uint32_t nrounds, const SfArgs* sf, uint64_t* codes,
                    uint64_t* rank, hipStream_t s)
@@ -1058,13 +1094,7 @@ int solve_by_layer(const PeelState& st, const MphfLayout& L, uint32_t nrounds, c
         else
             HIP_TRY(launch_assign_round(L.slots, L.lstart, (uint32_t)r, cnt, st.P, code8, 16384, s));
     }
-    if (!sf) {
-        Timed tm(PH_RANK, s);
-        HIP_TRY(launch_pack_count(code8, st.m, codes, L.bcount, s));
-        const uint64_t nblocks = (st.m + 511) / 512;
-        HIP_TRY(launch_scan_u32_to_u64(L.bcount, nblocks, rank, nblocks, L.scan, L.scan_bytes, s));
-    }
-    return MPHX_OK;
+    return sf ? MPHX_OK : pack_codes_and_rank(st, L, codes, rank, s);
 }
 
 // The MPHF (codes + rank) or, with sf, the static function (codes = its packed fields).
@@ -1154,6 +1184,7 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
     st.dcount = L.dcount;
     st.aux = L.aux;
     st.sync = L.sync;
+    st.wait = group_wait_ticks();
 
     Ctrl h{};
     uint64_t peeled = 0;
@@ -1272,10 +1303,16 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
             HIP_TRY(hipStreamSynchronize(s));
             info->layer0 = l0;
         }
-        if (m * (sf ? sf_elem_bytes(mphx_sf_bits(sf->sigma)) : 1) <= kSolveGridMaxBytes) {
+        const uint64_t bytes = m * (sf ? sf_elem_bytes(mphx_sf_bits(sf->sigma)) : 1);
+        if (bytes <= kSolveGridMaxBytes) {
             st.grid_cap = (unsigned)g_opt.grid.load();
             HIP_TRY(launch_sync_zero(st, s));
+            HIP_TRY(launch_zero(L.rec, bytes, s));
             HIP_TRY(solve(h.nrounds));
+            if (!sf) {
+                int rc = pack_codes_and_rank(st, L, codes, rank, s);
+                if (rc) return rc;
+            }
         } else {
             int rc = solve_by_layer(st, L, h.nrounds, sf, codes, rank, s);
             if (rc) return rc;

@@ -267,35 +267,60 @@ __global__ __launch_bounds__(kBinAccBlock) void k_bins_accum(BinArgs a, uint64_t
 __global__ __launch_bounds__(kBinAccBlock) void k_bins_again(BinArgs a, const uint32_t* __restrict__ edges,
                                                              uint64_t* __restrict__ ones, uint2* __restrict__ sums,
                                                              uint32_t* __restrict__ state, Ctrl* ctrl,
-                                                             GridSync* sync)
+                                                             GridSync* sync, uint32_t wait)
 {
-    __shared__ uint32_t s_join[2], s_sum[2];
+    __shared__ uint32_t s_join[3], s_sum[2];
     __shared__ uint64_t s_total;
     for (uint64_t i = (uint64_t)blockIdx.x * kBinAccBlock + threadIdx.x; i < a.n; i += (uint64_t)gridDim.x * kBinAccBlock)
         state[i] = kUnclaimed;
     if (*a.full == 0)
         return;
     Grid g;
-    if (!grid_join(sync, g, s_join))
+    if (!grid_join<true>(sync, g, s_join, wait))
         return;
-    const uint64_t first = (uint64_t)g.rank * kBinAccBlock + threadIdx.x, stride = (uint64_t)g.members * kBinAccBlock;
-    for (uint64_t v = first; v < a.m; v += stride)
-        ag_store(a.rec + v, (uint64_t)0);
-    grid_barrier(g, &s_total);
-    for (uint64_t e = first; e < a.n; e += stride) {
-        const uint32_t x = edges[3 * e], y = edges[3 * e + 1], z = edges[3 * e + 2];
-        if (bad_edge(x, y, z, a.m))
-            continue;  // reported by k_bins
-        Rec::add(a.rec, x, (uint32_t)e);
-        Rec::add(a.rec, y, (uint32_t)e);
-        Rec::add(a.rec, z, (uint32_t)e);
+    // the records cleared, the edges added, the buckets summed up; a group that is not whole goes
+    // through each in spans, with a chance to grow behind each
+    uint32_t stage = 0;
+    uint64_t pos = 0;
+    if (g.phase) {
+        stage = (uint32_t)ag_load(&g.s->run[0]);
+        pos = ag_load(&g.s->run[1]);
     }
-    grid_barrier(g, &s_total);
-    for (uint32_t b = g.rank; b < a.nb; b += g.members) {
-        const uint64_t* const rec = a.rec + ((uint64_t)b << a.shift);
-        bucket_summary(a, b, ones, sums, ctrl, [&](uint32_t j) { return ag_load(rec + j); }, s_sum);
-        __syncthreads();
+    while (stage < 3) {
+        const uint64_t total = stage == 0 ? a.m : (stage == 1 ? a.n : a.nb);
+        const uint64_t stride = (uint64_t)g.members * (stage < 2 ? kBinAccBlock : 1u);
+        const uint64_t first = stage < 2 ? (uint64_t)g.rank * kBinAccBlock + threadIdx.x : g.rank;
+        const uint64_t to = g.whole() ? total : min(total, pos + stride * (stage < 2 ? kGridSpan : 1u));
+        if (stage == 0) {
+            for (uint64_t v = pos + first; v < to; v += stride)
+                ag_store(a.rec + v, (uint64_t)0);
+        } else if (stage == 1) {
+            for (uint64_t e = pos + first; e < to; e += stride) {
+                const uint32_t x = edges[3 * e], y = edges[3 * e + 1], z = edges[3 * e + 2];
+                if (bad_edge(x, y, z, a.m))
+                    continue;  // reported by k_bins
+                Rec::add(a.rec, x, (uint32_t)e);
+                Rec::add(a.rec, y, (uint32_t)e);
+                Rec::add(a.rec, z, (uint32_t)e);
+            }
+        } else {
+            for (uint64_t b = pos + first; b < to; b += stride) {
+                const uint64_t* const rec = a.rec + (b << a.shift);
+                bucket_summary(a, (uint32_t)b, ones, sums, ctrl, [&](uint32_t j) { return ag_load(rec + j); }, s_sum);
+                __syncthreads();
+            }
+        }
+        pos = to;
+        if (to == total) {
+            stage++;
+            pos = 0;
+        }
+        grid_barrier<true>(g, &s_total);
+        if (g.grew && g.rank == 0 && threadIdx.x == 0)
+            grid_admit(g, stage, pos);
     }
+    if (g.rank == 0 && threadIdx.x == 0)
+        grid_done(g);
 }
 
 // Round 0: the hinges of layer 0 write their edges' states and append the edges.  Block 0 also adds
@@ -455,7 +480,7 @@ hipError_t launch_bins_accum(const PeelState& st, uint32_t shift, hipStream_t s)
     k_bins_accum<<<a.nb, kBinAccBlock, 8ull << shift, s>>>(a, ones, sums, st.ctrl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_bins_again<<<kGridMax, kBinAccBlock, 0, s>>>(a, st.edges, ones, sums, st.state, st.ctrl, st.sync + 2);
+    k_bins_again<<<kGridMax, kBinAccBlock, 0, s>>>(a, st.edges, ones, sums, st.state, st.ctrl, st.sync + 2, st.wait);
     return hipGetLastError();
 }
 

@@ -37,7 +37,7 @@ struct Ctrl {
     unsigned long long run_lo;   // where the next launch goes on: start of layer run_r,
     unsigned long long run_list; // its edges in the shared list,
     uint32_t run_r;              // and the round
-    uint32_t pad32;
+    uint32_t joined;             // workgroups that joined a group after it had begun
     uint64_t pad[17];
 };
 static_assert(sizeof(Ctrl) == 256, "Ctrl is one 256-byte slot");

@@ -45,6 +45,7 @@ struct PeelState {
     uint32_t* vout;
     void* aux;              // partition histograms and scan scratch (part_aux_bytes)
     struct GridSync* sync;  // three groups' barrier state (rounds.hip, bins.hip)
+    uint32_t wait;          // ticks of 10 ns that a group waits for its whole grid before it begins
 };
 
 // utilities (scan.hip)
@@ -146,14 +147,17 @@ size_t run_sync_bytes();
 hipError_t launch_run_init(const PeelState& st, uint64_t zero_words, hipStream_t s);
 // A layer of more than limit edges ends the launch too, all of it in the slots (edge ids, hinges in
 // the states) and its size in lcount.
-hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, hipStream_t s);
+// Without `grow` the launch does nothing (ctrl->nrounds and run_r as before) unless its whole grid finds room
+// at once; with it the group begins smaller and grows.
+hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, bool grow, hipStream_t s);
 // Before launch_rounds on layer r of a claim-list run: the layer's states (all others unclaimed, in
 // st.state, by the caller), the run's place, zeroed barrier words.
 hipError_t launch_rounds_resume(const PeelState& st, uint32_t r, hipStream_t s);
 hipError_t launch_rounds_again(const PeelState& st, hipStream_t s);
 // All layers of a complete peel of nrounds rounds in one launch, any size; the MPHF's codes and
 // rank samples, or a static function's values u (over the records).  nrounds 0: enqueued behind
-// launch_rounds before its outcome is known, does nothing after an incomplete peel.
+// launch_rounds before its outcome is known, does nothing after an incomplete peel; else only the
+// layers: the caller clears the codes or values before, and packs the codes behind.
 // st.sync[1] is zeroed: by launch_run_init, else by launch_sync_zero.
 hipError_t launch_sync_zero(const PeelState& st, hipStream_t s);
 hipError_t launch_copy_ctrl(const Ctrl* ctrl, Ctrl* out, hipStream_t s);

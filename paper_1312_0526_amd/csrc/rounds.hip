@@ -25,7 +25,7 @@ namespace mphx {
 constexpr uint32_t kRoundsBlock = 512;
 constexpr uint32_t kPrivate = 4096;          // edges of a workgroup's own list
 constexpr uint32_t kPrivateBits = 21;        // a barrier's payload: edges of private lists, then of the shared one
-static_assert(kPrivate * kGridMax < 1u << kPrivateBits && kPrivateBits + 32 <= 54, "both counts fit");
+static_assert(kPrivate * kGridMax < 1u << kPrivateBits && kPrivateBits + 32 <= 53, "both counts fit");
 // Every so many rounds all edges of the next layer go through the shared list, which deals them out
 // evenly: the private lists grow by descent, and without it one of 122 workgroups held 4 times its
 // share of a layer after 50 rounds at 10^6 keys.  The rounds took 397, 386, 385 and 412 us with a deal
@@ -82,6 +82,7 @@ struct RoundsArgs {
     GridSync* sync;
     uint64_t n, P, rcap;
     uint64_t limit;  // a layer beyond it ends the launch
+    uint32_t wait;   // grid_join's
     const uint32_t* vin;  // static functions: see PeelState
     uint32_t* vout;
 };
@@ -91,39 +92,61 @@ struct RoundsArgs {
 // The edge of layer r is deleted at its vertices other than the hinge; the delete that takes a
 // vertex from degree 2 to 1 claims the vertex's last edge for round r + 1 (lowest position wins)
 // and its first claimer appends the edge, as in k_apply.
-template <int kR, bool kTri, int kShift>
-__global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
+//
+// kGrow: the group may begin without the whole grid.  What it takes to grow costs rounds 5 to 14% in registers
+// alone (453 against 490 us a build at 4x10^4 keys), so a group that is whole at once has a kernel of its own.
+struct RoundsShared {
+    uint32_t list[2][kPrivate];
+    uint32_t next[2], join[3];
+    uint64_t total, off;
+    unsigned long long push, claims;
+};
+
+template <int kR, bool kTri, int kShift, bool kGrow>
+__device__ __forceinline__ void peel_rounds(const RoundsArgs& a, Grid& g, RoundsShared& sh)
 {
     static_assert(!kTri || kR == 3, "parts hold one vertex each");
-    __shared__ uint32_t s_list[2][kPrivate];
-    __shared__ uint32_t s_next[2], s_join[2];
-    __shared__ uint64_t s_total, s_off;
-    __shared__ unsigned long long s_push, s_claims;
-    Grid g;
-    if (!grid_join(a.sync, g, s_join))
-        return;
+    auto& s_list = sh.list;
+    auto& s_next = sh.next;
+    uint64_t &s_total = sh.total, &s_off = sh.off;
+    unsigned long long &s_push = sh.push, &s_claims = sh.claims;
+    Ctrl* const c = a.ctrl;
     const uint32_t tid = threadIdx.x;
     const bool lead = g.rank == 0 && tid == 0;
-    Ctrl* const c = a.ctrl;
-    uint64_t lo = c->run_lo, glist = c->run_list;
-    uint32_t r = c->run_r;
-    if (r == 0) {
-        // a degree above 255 (see k_round0) or a bad edge: nothing may be read off the records
-        if ((c->err & (kErrDegree | kErrBadEdge)) || c->degsum != (uint64_t)kR * a.n)
-            return;
-        glist = a.lcount[0];
-        if (lead) {
-            c->f0 = c->ftail;  // before any member adds to it
-            c->layer0 = glist;
-        }
-    }
+    uint64_t lo = c->run_lo, glist = c->run_list, pos = 0;  // pos: the shared list's edges that are done
+    uint32_t r = c->run_r, done = 0;
     // Edges of private lists, a cursor for even and one for odd rounds: a member moves it after it has
     // arrived, so others may be one round ahead of it, but not two.
     GridLine* const pcur = a.sync->cursor;
     unsigned long long* const gcur = &a.sync->cursor[2].w;  // edges of shared lists, all rounds
     uint64_t psum = 0, pother = 0, gsum = 0;  // what the cursors passed before this round
     uint64_t ptot = 0;            // this layer's private edges
-    uint32_t pc = 0, cur = 0, done = 0;
+    uint32_t pc = 0, cur = 0;
+    if (!kGrow || g.phase == 0) {
+        if (r == 0) {
+            glist = a.lcount[0];
+            if (lead) {
+                c->f0 = c->ftail;  // before any member adds to it
+                c->layer0 = glist;
+            }
+        }
+    } else {  // the place that admit() below gives
+        auto place = [&](uint32_t q) { return uniform64(ag_load(&g.s->run[q])); };
+        r = (uint32_t)place(0);
+        done = (uint32_t)place(1);
+        lo = place(2);
+        glist = place(3);
+        pos = place(4);
+        ptot = place(5);
+        psum = place(6);
+        pother = place(7);
+        gsum = place(8);
+    }
+    auto admit = [&](uint32_t round, uint32_t rounds) {
+        if (kGrow && g.grew && lead)
+            grid_admit(g, round, rounds, lo, glist, pos, ptot, psum, pother, gsum);
+    };
+    bool fresh = kGrow && g.grew;  // members without private edges: the next layer is dealt out
     uint64_t pbase = 0;
     unsigned long long mypush = 0, myclaims = 0;
     // this thread's first private edge and its vertices, loaded while the group waited
@@ -242,9 +265,18 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
         }
         for (uint32_t i = tid + kRoundsBlock; i < pc; i += kRoundsBlock)
             peel(s_list[cur][i], pbase + i);
-        for (uint64_t j = member_first(g); j < glist; j += member_stride(g))
-            peel(ag_load(&a.slots[lo + j].x), lo + j);
-        if (g.members > 1 && done % kDealRounds == kDealRounds - 1) {
+        for (;;) {
+            const uint64_t to = !kGrow || g.whole() ? glist : min(glist, pos + member_stride(g) * kGridSpan);
+            for (uint64_t j = pos + member_first(g); j < to; j += member_stride(g))
+                peel(ag_load(&a.slots[lo + j].x), lo + j);
+            if (!kGrow || to == glist)
+                break;
+            pos = to;
+            grid_barrier<kGrow>(g, &s_total);
+            fresh |= g.grew;
+            admit(r, done);
+        }
+        if (g.members > 1 && (fresh || done % kDealRounds == kDealRounds - 1)) {
             __syncthreads();
             const uint32_t p = min(*count, cap);
             if (tid == 0)
@@ -253,10 +285,11 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
             for (uint32_t i = tid; i < p; i += kRoundsBlock)
                 ag_store(&a.slots[hi + (s_off - gsum) + i].x, next[i]);
             cap = 0;
+            fresh = false;
         }
         uint32_t pnext = 0;
         uint64_t off = 0;
-        const uint64_t total = grid_barrier(
+        const uint64_t total = grid_barrier<kGrow>(
             g, &s_total,
             [&]() -> uint64_t {
                 const uint32_t k = *count, p = min(k, cap);
@@ -294,8 +327,17 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
         pother = passed;
         gsum += glist;
         cur ^= 1;
+        if constexpr (kGrow) {
+            pos = 0;
+            fresh |= g.grew;
+            admit(r + 1, done + 1);
+        }
     }
     if (lead) {
+        if constexpr (kGrow) {
+            grid_done(g);
+            c->joined += g.members - g.first;
+        }
         if (more) {
             a.lcount[r] = glist;
             c->run_lo = lo;
@@ -315,6 +357,23 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
     }
 }
 
+// Without kGrow a group that does not find room for its whole grid leaves everything as it is, and the caller
+// launches the other kind.
+template <int kR, bool kTri, int kShift, bool kGrow>
+__global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
+{
+    __shared__ RoundsShared sh;
+    // a degree above 255 (see k_round0) or a bad edge: nothing may be read off the records, and every
+    // workgroup leaves.  (A launch that goes on from a later round has passed this.)
+    if (a.ctrl->run_r == 0 &&
+        ((a.ctrl->err & (kErrDegree | kErrBadEdge)) || a.ctrl->degsum != (uint64_t)kR * a.n))
+        return;
+    Grid g;
+    if (!grid_join<kGrow>(a.sync, g, sh.join, a.wait))
+        return;
+    peel_rounds<kR, kTri, kShift, kGrow>(a, g, sh);
+}
+
 // The layers of a complete peel, last first, with a barrier after each: load(i) reads slot i, which
 // nobody changes, and solve(item) solves it; a thread's first slot of the next layer is read while
 // the group waits.  The layers at the end of a peel hold few edges: member 0 alone goes through
@@ -324,22 +383,35 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
 // no layer but the top ones is that small, the test itself costs 10 us.
 constexpr uint32_t kLayerChunk = 1024;
 constexpr uint64_t kHopMax = 100'000;  // keys
-template <bool kHop, class Item, class Load, class Solve>
-__device__ __forceinline__ void solve_layers(Grid& g, const uint64_t* __restrict__ lstart, uint32_t nrounds,
-                                             uint64_t* s_ls, uint64_t* s_total, Load load, Solve solve)
+template <bool kHop, bool kGrow, class Item, class Load, class Solve>
+__device__ __forceinline__ void solve_layers_as(Grid& g, const uint64_t* __restrict__ lstart, uint32_t nrounds,
+                                                Ctrl* ctrl, uint64_t* s_ls, uint64_t* s_total, Load load,
+                                                Solve solve)
 {
     const uint32_t tid = threadIdx.x;
-    const uint64_t first = member_first(g), stride = member_stride(g);
-    bool solo = true, have = false;
+    const bool lead = g.rank == 0 && tid == 0;
+    uint64_t first = member_first(g), stride = member_stride(g);
+    bool solo = !(kGrow && g.grew), have = false;
+    // a workgroup that is taken in goes on with layer left - 1, from slot `resume` on
+    uint32_t left = nrounds;
+    uint64_t resume = 0;
+    if (kGrow && g.grew) {
+        left = uniform((uint32_t)ag_load(&g.s->run[0]));
+        resume = uniform64(ag_load(&g.s->run[1]));
+    }
     Item ahead{};
     uint32_t top = nrounds;  // layers [base, top) have their bounds in s_ls
     while (top > 0) {
         const uint32_t base = top > kLayerChunk ? top - kLayerChunk : 0;
+        if (kGrow && base >= left) {
+            top = base;
+            continue;
+        }
         __syncthreads();
         for (uint32_t k = tid; k <= top - base; k += kRoundsBlock)
             s_ls[k] = lstart[base + k];
         __syncthreads();
-        for (uint32_t k = top - base; k-- > 0;) {
+        for (uint32_t k = (kGrow ? min(top, left) : top) - base; k-- > 0;) {
             const uint64_t lo = s_ls[k], hi = s_ls[k + 1];
             const uint64_t below = k ? s_ls[k - 1] : lo;  // the next layer is [below, lo)
             if (hi - lo <= kRoundsBlock && (solo || (kHop && k && lo - below <= kRoundsBlock))) {
@@ -360,28 +432,55 @@ __device__ __forceinline__ void solve_layers(Grid& g, const uint64_t* __restrict
             }
             if (solo) {
                 solo = have = false;
-                grid_barrier(g, s_total);
+                grid_barrier<false>(g, s_total);
             }
-            uint64_t i = lo + first;
-            if (i < hi) {
-                solve(have ? ahead : load(i));
-                for (i += stride; i < hi; i += stride)
-                    solve(load(i));
-            }
-            have = k != 0;
-            grid_barrier(
-                g, s_total, []() -> uint64_t { return 0; },
-                [&] {
-                    if (have && below + first < lo)
-                        ahead = load(below + first);
-                });
+            uint64_t from = kGrow ? max(lo, resume) : lo, to;
+            resume = 0;
+            do {
+                to = !kGrow || g.whole() ? hi : min(hi, from + stride * kGridSpan);
+                uint64_t i = from + first;
+                if (i < to) {
+                    solve(have ? ahead : load(i));
+                    for (i += stride; i < to; i += stride)
+                        solve(load(i));
+                }
+                have = k != 0 && to == hi;
+                grid_barrier<kGrow>(
+                    g, s_total, []() -> uint64_t { return 0; },
+                    [&] {
+                        if (have && below + first < lo)
+                            ahead = load(below + first);
+                    });
+                if (kGrow && g.grew) {
+                    first = member_first(g);
+                    stride = member_stride(g);
+                    have = false;
+                    if (lead)
+                        grid_admit(g, base + k + (to == hi ? 0u : 1u), to == hi ? 0ull : to);
+                }
+                from = to;
+            } while (to != hi);
         }
         top = base;
     }
     if (solo)
-        grid_barrier(g, s_total);
+        grid_barrier<false>(g, s_total);
+    if (kGrow && lead) {
+        grid_done(g);
+        ctrl->joined += g.members - g.first;
+    }
+}
+template <bool kHop, class Item, class Load, class Solve>
+__device__ __forceinline__ void solve_layers(Grid& g, const uint64_t* __restrict__ lstart, uint32_t nrounds,
+                                             Ctrl* ctrl, uint64_t* s_ls, uint64_t* s_total, Load load, Solve solve)
+{
+    if (!g.grew && g.whole())  // since the beginning
+        solve_layers_as<kHop, false, Item>(g, lstart, nrounds, ctrl, s_ls, s_total, load, solve);
+    else
+        solve_layers_as<kHop, true, Item>(g, lstart, nrounds, ctrl, s_ls, s_total, load, solve);
 }
 
+// By the group that begins the run: a barrier follows.
 __device__ __forceinline__ void zero_shared(Grid& g, uint64_t* p, uint64_t words)
 {
     for (uint64_t i = member_first(g); i < words; i += member_stride(g))
@@ -390,33 +489,40 @@ __device__ __forceinline__ void zero_shared(Grid& g, uint64_t* p, uint64_t words
 
 // The whole rest of an MPHF build whose peel is complete: the codes (one byte per vertex, over
 // the records), layer by layer; the packed codes and rank samples, each member's share of the
-// vertices after a prefix over the members.  Does nothing after an incomplete peel.
+// vertices after a prefix over the members.  Does nothing after an incomplete peel.  With nrounds
+// given only the layers, over codes that are zero: clearing and packing up to 2^30 of them would be
+// kept from growing with the group.
 template <bool kHop>
 __global__ __launch_bounds__(kRoundsBlock) void k_mphf_finish(const uint3* __restrict__ slots,
-                                                              const uint64_t* __restrict__ lstart, const Ctrl* ctrl,
+                                                              const uint64_t* __restrict__ lstart, Ctrl* ctrl,
                                                               GridSync* sync, uint32_t nrounds, uint64_t n, uint64_t m,
                                                               uint64_t P, uint64_t* code_words, uint64_t* __restrict__ codes,
-                                                              uint64_t* __restrict__ rank, uint32_t* bcount)
+                                                              uint64_t* __restrict__ rank, uint32_t* bcount, uint32_t wait)
 {
-    __shared__ uint32_t s_join[2];
+    __shared__ uint32_t s_join[3];
     __shared__ uint64_t s_total, s_ls[kLayerChunk + 1], s_wave[kRoundsBlock / kWave], s_carry;
-    if (nrounds == 0) {  // enqueued behind launch_rounds
+    const bool rest = nrounds == 0;  // enqueued behind launch_rounds
+    if (rest) {
         nrounds = ctrl->nrounds;
         if (nrounds == 0xFFFFFFFFu || ctrl->peeled != n)
             return;
     }
     Grid g;
-    if (!grid_join(sync, g, s_join))
+    if (!grid_join<true>(sync, g, s_join, wait))
         return;
     uint8_t* const code8 = reinterpret_cast<uint8_t*>(code_words);
-    zero_shared(g, code_words, (m + 7) / 8);  // 8m bytes of records hold it
-    grid_barrier(g, &s_total);
-    solve_layers<kHop, uint3>(g, lstart, nrounds, s_ls, &s_total, [&](uint64_t i) { return slots[i]; }, [&](uint3 t) {
+    if (rest && g.phase == 0) {
+        zero_shared(g, code_words, (m + 7) / 8);  // 8m bytes of records hold it
+        grid_barrier<false>(g, &s_total);
+    }
+    solve_layers<kHop, uint3>(g, lstart, nrounds, ctrl, s_ls, &s_total, [&](uint64_t i) { return slots[i]; }, [&](uint3 t) {
         const uint32_t k = part_of(t.x, P);
         const uint32_t ca = ag_load(code8 + t.y), cb = ag_load(code8 + t.z);
         const uint32_t x = (k + 6 - (ca == 3 ? 0u : ca) - (cb == 3 ? 0u : cb)) % 3;
         ag_store(code8 + t.x, (uint8_t)(x ? x : 3));
     });
+    if (!rest)
+        return;
     // this member's rank blocks [b0, b1) of 512 vertices, one thread per code word of 32
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const uint64_t nwords = (m + 31) / 32, nb = (m + 511) / 512, per = (nb + g.members - 1) / g.members;
@@ -462,7 +568,7 @@ __global__ __launch_bounds__(kRoundsBlock) void k_mphf_finish(const uint3* __res
         ag_store(&sync->sums[g.rank], (unsigned long long)t);
         s_carry = 0;
     }
-    grid_barrier(g, &s_total);
+    grid_barrier<false>(g, &s_total);
     if (wv == 0) {  // hinges below this member's first vertex
         uint64_t t = 0;
         for (uint32_t q = lane; q < g.rank; q += kWave)
@@ -498,29 +604,33 @@ __global__ __launch_bounds__(kRoundsBlock) void k_mphf_finish(const uint3* __res
 }
 
 // The values u of a static function whose peel is complete (zero off the hinges), as
-// k_sf_assign_round solves them.  Does nothing after an incomplete peel.
+// k_sf_assign_round solves them.  Does nothing after an incomplete peel.  With nrounds given they
+// are zero already.
 template <typename T, bool kHop>
 __global__ __launch_bounds__(kRoundsBlock) void k_sf_solve(const uint3* __restrict__ slots,
                                                            const uint32_t* __restrict__ vals,
-                                                           const uint64_t* __restrict__ lstart, const Ctrl* ctrl,
+                                                           const uint64_t* __restrict__ lstart, Ctrl* ctrl,
                                                            GridSync* sync, uint32_t nrounds, uint64_t n, uint64_t m,
-                                                           uint64_t sigma, uint64_t* u_words)
+                                                           uint64_t sigma, uint64_t* u_words, uint32_t wait)
 {
-    __shared__ uint32_t s_join[2];
+    __shared__ uint32_t s_join[3];
     __shared__ uint64_t s_total, s_ls[kLayerChunk + 1];
-    if (nrounds == 0) {  // enqueued behind launch_rounds
+    const bool rest = nrounds == 0;  // enqueued behind launch_rounds
+    if (rest) {
         nrounds = ctrl->nrounds;
         if (nrounds == 0xFFFFFFFFu || ctrl->peeled != n)
             return;
     }
     Grid g;
-    if (!grid_join(sync, g, s_join))
+    if (!grid_join<true>(sync, g, s_join, wait))
         return;
     T* const u = reinterpret_cast<T*>(u_words);
-    zero_shared(g, u_words, (m * sizeof(T) + 7) / 8);
-    grid_barrier(g, &s_total);
+    if (rest && g.phase == 0) {
+        zero_shared(g, u_words, (m * sizeof(T) + 7) / 8);
+        grid_barrier<false>(g, &s_total);
+    }
     auto load = [&](uint64_t i) { return make_uint4(slots[i].x, slots[i].y, slots[i].z, vals[i]); };
-    solve_layers<kHop, uint4>(g, lstart, nrounds, s_ls, &s_total, load, [&](uint4 t) {
+    solve_layers<kHop, uint4>(g, lstart, nrounds, ctrl, s_ls, &s_total, load, [&](uint4 t) {
         uint64_t x = (uint64_t)t.w + 2 * sigma - ag_load(u + t.y) - ag_load(u + t.z);
         x = x >= sigma ? x - sigma : x;
         x = x >= sigma ? x - sigma : x;
@@ -582,32 +692,39 @@ hipError_t launch_rounds_resume(const PeelState& st, uint32_t r, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, hipStream_t s)
+template <bool kGrow>
+static hipError_t launch_rounds_as(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, hipStream_t s)
 {
     const RoundsArgs a{st.rec, st.edges, st.state, st.slots, st.lstart, st.lcount, st.ctrl, st.sync,
-                       st.n,   st.P,     st.rcap,  limit,    st.vin,    st.vout};
+                       st.n,   st.P,     st.rcap,  limit,    st.wait,   st.vin,    st.vout};
     const unsigned g = run_grid(st);
     if (st.tripartite) {
         if (r != 3 || generic_shift) return hipErrorInvalidValue;
-        k_rounds<3, true, 2><<<g, kRoundsBlock, 0, s>>>(a);
+        k_rounds<3, true, 2, kGrow><<<g, kRoundsBlock, 0, s>>>(a);
         return hipGetLastError();
     }
     if (!generic_shift) {
         if (r != 3) return hipErrorInvalidValue;
-        k_rounds<3, false, 2><<<g, kRoundsBlock, 0, s>>>(a);
+        k_rounds<3, false, 2, kGrow><<<g, kRoundsBlock, 0, s>>>(a);
         return hipGetLastError();
     }
     switch (r) {
-    case 2: k_rounds<2, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
-    case 3: k_rounds<3, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
-    case 4: k_rounds<4, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
-    case 5: k_rounds<5, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
-    case 6: k_rounds<6, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
-    case 7: k_rounds<7, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
-    case 8: k_rounds<8, false, 3><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 2: k_rounds<2, false, 3, kGrow><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 3: k_rounds<3, false, 3, kGrow><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 4: k_rounds<4, false, 3, kGrow><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 5: k_rounds<5, false, 3, kGrow><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 6: k_rounds<6, false, 3, kGrow><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 7: k_rounds<7, false, 3, kGrow><<<g, kRoundsBlock, 0, s>>>(a); break;
+    case 8: k_rounds<8, false, 3, kGrow><<<g, kRoundsBlock, 0, s>>>(a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, bool grow, hipStream_t s)
+{
+    return grow ? launch_rounds_as<true>(st, r, generic_shift, limit, s)
+                : launch_rounds_as<false>(st, r, generic_shift, limit, s);
 }
 
 __global__ void k_copy_ctrl(const uint64_t* __restrict__ ctrl, uint64_t* __restrict__ out)
@@ -629,7 +746,7 @@ hipError_t launch_mphf_finish(const PeelState& st, uint32_t nrounds, uint64_t* c
 {
     auto* const finish = st.n <= kHopMax ? k_mphf_finish<true> : k_mphf_finish<false>;
     finish<<<run_grid(st), kRoundsBlock, 0, s>>>(st.slots, st.lstart, st.ctrl, st.sync + 1, nrounds, st.n, st.m, st.P,
-                                                 st.rec, codes, rank, bcount);
+                                                 st.rec, codes, rank, bcount, st.wait);
     return hipGetLastError();
 }
 
@@ -638,7 +755,7 @@ hipError_t launch_sf_solve(const PeelState& st, uint32_t nrounds, uint64_t sigma
     const unsigned g = run_grid(st);
 #define MPHX_SOLVE(T)                                                                                               \
     (st.n <= kHopMax ? k_sf_solve<T, true> : k_sf_solve<T, false>)<<<g, kRoundsBlock, 0, s>>>(                      \
-        st.slots, st.vout, st.lstart, st.ctrl, st.sync + 1, nrounds, st.n, st.m, sigma, st.rec)
+        st.slots, st.vout, st.lstart, st.ctrl, st.sync + 1, nrounds, st.n, st.m, sigma, st.rec, st.wait)
     switch (sf_elem_bytes(b)) {
     case 1: MPHX_SOLVE(uint8_t); break;
     case 2: MPHX_SOLVE(uint16_t); break;
