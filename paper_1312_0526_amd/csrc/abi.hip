@@ -999,7 +999,7 @@ struct SfArgs {
 };
 
 // String keys beyond this many are hashed by a launch of their own (6 us), whose workgroups share them;
-// one workgroup hashes fewer at once (two keys a thread).
+// one workgroup hashes fewer at once (two keys a thread), unless they are long (k_small_build).
 constexpr uint64_t kSmallStrHash = 2048;
 constexpr uint32_t kFirstTryAgain = 0xFFFFFFFFu;
 
@@ -1015,32 +1015,39 @@ int small_build(const KeySrc& k, uint64_t n, uint64_t seed, uint64_t P, uint32_t
     } else {
         a.bytes = k.bytes;
         a.offs = k.offs;
-        if (n > kSmallStrHash) {
-            Timed tm(PH_HASH, s);
-            HIP_TRY(launch_hash_str(k.bytes, k.offs, n, seed, P, L.edges, nullptr, PartHist1{nullptr, 0, 0}, s));
-            a.edges = L.edges;
-        }
     }
     a.n = (uint32_t)n;
     a.P = (uint32_t)P;
-    a.seed = seed;
-    a.max_tries = max_tries;
     a.queue = reinterpret_cast<uint16_t*>(L.rec);
     a.start = reinterpret_cast<uint32_t*>(L.lstart);
     a.codes = codes;
     a.rank = rank;
-    HostSlot slot;
-    a.out = slot.get() ? (LdsOutcome*)slot.get() : (LdsOutcome*)L.ctrl;
-    {
-        Timed tm(PH_APPLY, s);
-        HIP_TRY(launch_small_build(a, s));
-    }
     LdsOutcome o{};
-    if (!slot.get()) HIP_TRY(hipMemcpyAsync(&o, L.ctrl, sizeof o, hipMemcpyDeviceToHost, s));
-    const hipError_t e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return fail(MPHX_EDEVICE, "hipStreamSynchronize failed: %s", hipGetErrorString(e));
-    if (slot.get()) memcpy(&o, slot.get(), sizeof o);
-    g_timers.harvest();
+    uint32_t made = 0;  // tries
+    bool hash = k.kind == MPHX_KEYS_STR && n > kSmallStrHash;
+    do {
+        a.seed = seed + made;
+        a.max_tries = max_tries - made;
+        a.edges = hash ? L.edges : nullptr;
+        if (hash) {
+            Timed tm(PH_HASH, s);
+            HIP_TRY(launch_hash_str(k.bytes, k.offs, n, a.seed, P, L.edges, nullptr, PartHist1{nullptr, 0, 0}, s));
+        }
+        HostSlot slot;
+        a.out = slot.get() ? (LdsOutcome*)slot.get() : (LdsOutcome*)L.ctrl;
+        {
+            Timed tm(PH_APPLY, s);
+            HIP_TRY(launch_small_build(a, s));
+        }
+        if (!slot.get()) HIP_TRY(hipMemcpyAsync(&o, L.ctrl, sizeof o, hipMemcpyDeviceToHost, s));
+        const hipError_t e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return fail(MPHX_EDEVICE, "hipStreamSynchronize failed: %s", hipGetErrorString(e));
+        if (slot.get()) memcpy(&o, slot.get(), sizeof o);
+        g_timers.harvest();
+        made += o.tries;
+        hash = true;
+    } while (o.status == kLdsHash);
+    o.tries = made;
     if (o.status) {
         first = o.tries - 1;
         if (first == 0) first = kFirstTryAgain;

@@ -1138,7 +1138,7 @@ __device__ __forceinline__ uint32_t build_lds_buckets(const BatchArgs& a, uint8_
             n = d.n;
             const uint64_t P = part_size_dev(n, a.gnum, a.gden);
             const uint64_t total = d.keys ? 0 : d.offs[n];
-            auto slow = [&](uint64_t) { return !d.keys; };
+            auto slow = [&](uint64_t) -> int32_t { return d.keys ? 0 : 1; };
             auto fetch = [&](uint32_t i, uint64_t sd) -> ulonglong2 {
                 uint64_t x, y;
                 key_digest(a, d, i, sd, x, y);

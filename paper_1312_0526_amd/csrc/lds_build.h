@@ -51,10 +51,11 @@ __host__ __device__ constexpr uint32_t lds_build_bytes(uint32_t m, bool queue)
 }
 
 constexpr int32_t kLdsTooDense = 2;  // a degree above 63 (or rounds that nothing holds): the try is not made
+constexpr int32_t kLdsHash = 3;      // the next try's strings are for a launch of their own to hash
 struct LdsOutcome {
     uint64_t seed;
     uint32_t tries;
-    int32_t status;  // 0; 1: a 2-core remained on every try; kLdsTooDense
+    int32_t status;  // 0; 1: a 2-core remained on every try; kLdsTooDense; kLdsHash
     uint32_t rounds, peeled, frontier0, frontier, claims, layer0;  // of the last try
 };
 
@@ -78,7 +79,7 @@ __device__ __forceinline__ uint32_t queue_reserve(uint32_t* tail, bool want1, bo
 // locals(key, sd) gives its three part-local vertices; kAhead reads are in flight at once, unless
 // slow(sd), where digest(i, sd) takes fetch's place: kAhead copies of a string's hashing cost more
 // in instruction fetches than they hide (a served request of 3,638 strings took 269 us with four,
-// 208 with one).
+// 208 with one).  slow(sd) is 0, 1 or kLdsHash, which ends the build before that try.
 // lds: lds_build_bytes(m, kQueueLds) bytes, 16-byte aligned; gqueue: m entries in device memory,
 // used unless kQueueLds; gstart: n + 2 words in device memory, or null: then a peel of kLdsRounds
 // rounds or more is left to the general path too.
@@ -107,6 +108,11 @@ __device__ LdsOutcome lds_build(uint32_t n, uint32_t P, uint64_t seed, uint32_t 
     LdsOutcome out{seed, 0, 1, 0, 0, 0, 0, 0, 0};
     for (uint32_t t = 0; t < max_tries; t++) {
         const uint64_t sd = seed + t;
+        const int32_t how = slow(sd);
+        if (how == kLdsHash) {
+            out.status = kLdsHash;
+            return out;
+        }
         out.seed = sd;
         out.tries = t + 1;
         for (uint32_t v = tid; v < m; v += kBlock)
@@ -131,7 +137,7 @@ __device__ LdsOutcome lds_build(uint32_t n, uint32_t P, uint64_t seed, uint32_t 
             if (max(d0 >> s0 & 255u, max(d1 >> s1 & 255u, d2 >> s2 & 255u)) >= kMaxLdsDegree)
                 st.err = 1;
         };
-        if (slow(sd)) {
+        if (how) {
 #pragma unroll 1
             for (uint32_t i = tid; i < n; i += kBlock)
                 insert(locals(digest(i, sd), sd));
