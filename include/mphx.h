@@ -589,8 +589,9 @@ MPHX_API int mphx_gen_str_bytes(uint8_t* bytes, const uint64_t* offs, uint64_t n
  *   "grid"        blocks per launch of the peeling kernels (0 = automatic).  Up to 2^24 edges
  *                 all rounds share one launch of at most 256 512-thread blocks (automatic: one
  *                 per 4096 to 40960 edges), as do the assignment's layers up to 2^30 bytes of
- *                 vertex values; above, each round is a grid-stride launch (automatic: one
- *                 256-thread block per 256 edges of the layer, between 64 and 1024).
+ *                 vertex values; above, and for large layers of more than 2^22 edges, each round is a
+ *                 grid-stride launch (automatic: one 256-thread block per 256 edges of the layer,
+ *                 between 64 and 1024).
  *   "round_batch" for rounds of a launch each: peeling rounds enqueued before the first check
  *                 of the termination flag (default 64; later checks come every 16 rounds).
  *                 Empty rounds past the end cost a launch each, a check a host round trip.

@@ -300,19 +300,23 @@ public:
 };
 static_assert(sizeof(Ctrl) <= HostSlot::kBytes && sizeof(LdsOutcome) <= HostSlot::kBytes, "a slot holds a report");
 
-int read_ctrl(Ctrl* dctrl, Ctrl& h, hipStream_t s)
+// layer (dev, nullable) is read into h.layer.
+int read_ctrl(Ctrl* dctrl, Ctrl& h, hipStream_t s, const unsigned long long* layer = nullptr)
 {
     HostSlot slot;
     if (slot.get()) {
         // the slot goes back only once the stream has passed the kernel that writes it
-        HIP_TRY(launch_copy_ctrl(dctrl, (Ctrl*)slot.get(), s));
+        HIP_TRY(launch_copy_ctrl(dctrl, layer, (Ctrl*)slot.get(), s));
         const hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) return fail(MPHX_EDEVICE, "hipStreamSynchronize failed: %s", hipGetErrorString(e));
         memcpy(&h, slot.get(), sizeof h);
         return MPHX_OK;
     }
     HIP_TRY(hipMemcpyAsync(&h, dctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
+    unsigned long long x = 0;
+    if (layer) HIP_TRY(hipMemcpyAsync(&x, layer, sizeof x, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    if (layer) h.layer = x;
     return MPHX_OK;
 }
 
@@ -346,38 +350,53 @@ int check_run_errors(const Ctrl& h, uint64_t n, uint64_t rcap, uint32_t r = 3)
 
 constexpr uint32_t kLaterBatch = 16;
 
-// Enqueue rounds in batches until a round finds an empty layer.  On return
-// h.nrounds holds the number of non-empty layers and *peeled the number of peeled edges.
-int run_rounds(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
+// One launch for all rounds keeps an eighth of the waves in flight that k_apply does, and claims beyond a
+// workgroup's list share one cursor, so in runs of more than kOwnLaunchMin edges the layers of more than
+// kOwnLaunchSize / r^2 edges get launches of their own first, read back two rounds at a time.  All rounds
+// in one launch, all in launches, and both in turn: 6.47, 4.65 and 3.79 ms for 1.6x10^7 u64 keys at gamma 2
+// (half the edges in layer 0), 3.20, 2.85 and 2.11 for 9x10^6; at gamma 1.23 4.59, 5.59 and 4.28, and 2.59,
+// 3.76 and 2.62; 6.39, 5.74 and 5.60 for 6.5x10^6 edges of 8 vertices, whose layer 0 holds some 3x10^5.
+// Below the least run one launch is the best (1.09 ms against 1.19 in turn at 2.5x10^6 keys, gamma 1.23).
+constexpr uint64_t kOwnLaunchMin = 1ull << 22, kOwnLaunchSize = 3ull << 22;
+constexpr uint32_t kHandoverBatch = 2;
+
+// Rounds of a launch each, enqueued in batches; h.layer comes as the edges of layer 0.  With small == 0
+// until a round finds an empty layer (h.nrounds non-empty ones); else until the layer of the round to
+// come is seen to hold at most `small` edges.  generic_shift: the apply of r-uniform lists.
+int run_rounds(PeelState& st, uint32_t r, bool generic_shift, uint64_t small, Ctrl& h, uint32_t& round, hipStream_t s)
 {
-    uint32_t r = 0;
-    uint32_t batch = (uint32_t)std::max(1, g_opt.round_batch.load());
-    unsigned long long next_layer = 0;
-    HIP_TRY(hipMemcpyAsync(&next_layer, st.lcount, sizeof next_layer, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    round = 0;
+    uint32_t batch = small ? kHandoverBatch : (uint32_t)std::max(1, g_opt.round_batch.load());
     for (;;) {
-        uint64_t upto = std::min<uint64_t>((uint64_t)r + batch, st.rcap);
+        if (small && h.layer <= small) return MPHX_OK;
+        const uint64_t upto = std::min<uint64_t>((uint64_t)round + batch, st.rcap);
         // sized for the next layer; later rounds of the batch may be larger, which only costs
         // them more grid-stride iterations
-        st.grid_cap = auto_grid(next_layer);
-        for (; r < upto; r++) {
+        st.grid_cap = auto_grid(h.layer);
+        for (; round < upto; round++) {
             Timed t(PH_APPLY, s);
-            HIP_TRY(launch_apply(st, r, false, ApplyMode::kAtomicClaims, s));
+            HIP_TRY(generic_shift ? launch_apply_r(st, r, round, s)
+                                  : launch_apply(st, round, false, ApplyMode::kAtomicClaims, s));
         }
-        HIP_TRY(hipMemcpyAsync(&next_layer, st.lcount + r, sizeof next_layer, hipMemcpyDeviceToHost, s));
-        int rc = read_ctrl(st.ctrl, h, s);
+        int rc = read_ctrl(st.ctrl, h, s, st.lcount + round);
         if (rc) return rc;
-        if (h.nrounds != 0xFFFFFFFFu) {
-            uint64_t p = 0;
-            HIP_TRY(hipMemcpyAsync(&p, st.lstart + h.nrounds, sizeof p, hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
-            *peeled = p;
-            return MPHX_OK;
-        }
-        if (r >= st.rcap)
+        if (!small && h.nrounds != 0xFFFFFFFFu) return MPHX_OK;
+        if (round >= st.rcap)
             return fail(MPHX_ERANGE, "more than %llu peeling rounds", (unsigned long long)st.rcap);
-        batch = kLaterBatch;
+        if (!small) batch = kLaterBatch;
     }
+}
+
+// All rounds so; *peeled: the edges removed.
+int run_rounds_launched(PeelState& st, uint32_t r, bool generic_shift, Ctrl& h, uint64_t* peeled, hipStream_t s)
+{
+    uint32_t round = 0;
+    int rc = read_ctrl(st.ctrl, h, s, st.lcount);
+    if (!rc) rc = run_rounds(st, r, generic_shift, 0, h, round, s);
+    if (rc) return rc;
+    HIP_TRY(hipMemcpyAsync(peeled, st.lstart + h.nrounds, sizeof *peeled, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    return MPHX_OK;
 }
 
 // Claim-list rounds.  Layer 0 comes from round 0's atomic claims, which keep it in vertex
@@ -512,9 +531,20 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
 template <class Finish>
 int run_rounds_grid(PeelState& st, uint32_t r, bool generic_shift, Ctrl& h, hipStream_t s, Finish finish)
 {
-    st.grid_cap = (unsigned)g_opt.grid.load();
     uint32_t joined = 0, from = 0;
     bool grow = false;
+    if (st.n > kOwnLaunchMin) {
+        int rc = read_ctrl(st.ctrl, h, s, st.lcount);
+        if (!rc) rc = check_run_errors(h, st.n, st.rcap, r);
+        if (rc) return rc;
+        // every batch of these rounds begins with a layer of more than `small` edges
+        const uint64_t f0 = h.ftail, small = kOwnLaunchSize / (r * r);
+        HIP_TRY(launch_zero(st.lcount + 1, (st.n / small + 2) * kHandoverBatch * sizeof(unsigned long long), s));
+        rc = run_rounds(st, r, generic_shift, small, h, from, s);
+        if (rc) return rc;
+        if (from) HIP_TRY(launch_rounds_from(st, from, f0, s));
+    }
+    st.grid_cap = (unsigned)g_opt.grid.load();
     for (;;) {
         {
             Timed t(PH_APPLY, s);
@@ -540,37 +570,6 @@ int check_build_errors(Ctrl* dctrl, uint64_t n, hipStream_t s, uint64_t& first_f
     if (rc) return rc;
     first_front = h.ftail;
     return check_run_errors(h, n, 0, r);
-}
-
-// The round loop of an r-hypergraph peel: as run_rounds, with the r-vertex apply.
-int run_rounds_r(PeelState& st, uint32_t r, Ctrl& h, uint64_t* peeled, hipStream_t s)
-{
-    uint32_t rd = 0;
-    uint32_t batch = (uint32_t)std::max(1, g_opt.round_batch.load());
-    unsigned long long next_layer = 0;
-    HIP_TRY(hipMemcpyAsync(&next_layer, st.lcount, sizeof next_layer, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    for (;;) {
-        uint64_t upto = std::min<uint64_t>((uint64_t)rd + batch, st.rcap);
-        st.grid_cap = auto_grid(next_layer);
-        for (; rd < upto; rd++) {
-            Timed t(PH_APPLY, s);
-            HIP_TRY(launch_apply_r(st, r, rd, s));
-        }
-        HIP_TRY(hipMemcpyAsync(&next_layer, st.lcount + rd, sizeof next_layer, hipMemcpyDeviceToHost, s));
-        int rc = read_ctrl(st.ctrl, h, s);
-        if (rc) return rc;
-        if (h.nrounds != 0xFFFFFFFFu) {
-            uint64_t p = 0;
-            HIP_TRY(hipMemcpyAsync(&p, st.lstart + h.nrounds, sizeof p, hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
-            *peeled = p;
-            return MPHX_OK;
-        }
-        if (rd >= st.rcap)
-            return fail(MPHX_ERANGE, "more than %llu peeling rounds", (unsigned long long)st.rcap);
-        batch = kLaterBatch;
-    }
 }
 
 }  // namespace
@@ -770,7 +769,7 @@ int mphx_peel(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t* order, ui
         peeled = h.peeled;
     } else {
         rc = check_build_errors(L.ctrl, n, s, f0);
-        if (!rc) rc = run_rounds(st, h, &peeled, s);
+        if (!rc) rc = run_rounds_launched(st, 3, false, h, &peeled, s);
     }
     if (rc) return rc;
 
@@ -854,7 +853,7 @@ int mphx_peel_r(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t r, uint3
         peeled = h.peeled;
     } else {
         rc = check_build_errors(L.ctrl, n, s, f0, r);
-        if (!rc) rc = run_rounds_r(st, r, h, &peeled, s);
+        if (!rc) rc = run_rounds_launched(st, r, true, h, &peeled, s);
     }
     if (rc) return rc;
     {
@@ -1269,7 +1268,7 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
                 if (info) { info->tries = t + 1; info->seed_used = sd; }
                 return rc;
             }
-            rc = st.lists ? run_rounds_lists(st, h, &peeled, s) : run_rounds(st, h, &peeled, s);
+            rc = st.lists ? run_rounds_lists(st, h, &peeled, s) : run_rounds_launched(st, 3, false, h, &peeled, s);
         }
         if (rc == kListOverflow) {  // redo this try with atomic claims
             g_opt.list_fallbacks++;

@@ -38,7 +38,8 @@ struct Ctrl {
     unsigned long long run_list; // its edges in the shared list,
     uint32_t run_r;              // and the round
     uint32_t joined;             // workgroups that joined a group after it had begun
-    uint64_t pad[17];
+    uint64_t pad[16];
+    unsigned long long layer;    // in a copy for the host: edges of the layer that it asked for
 };
 static_assert(sizeof(Ctrl) == 256, "Ctrl is one 256-byte slot");
 

@@ -134,8 +134,8 @@ hipError_t launch_close_layer(const PeelState& st, uint32_t r, hipStream_t s);
 enum class ApplyMode { kAtomicClaims, kClaimList, kUpdateList };
 // hinge_in_slot: layer r came from a resolved claim list
 hipError_t launch_apply(const PeelState& st, uint32_t r, bool hinge_in_slot, ApplyMode mode, hipStream_t s);
-// Runs of at most kRunMaxEdges edges (rounds.hip) peel in one launch: launch_run_init takes the
-// place of launch_ctrl_init; launch_round0 fills layer 0; launch_rounds peels until a layer is
+// Runs of at most kRunMaxEdges edges (rounds.hip) peel in one launch, large layers at their beginning
+// aside (launch_rounds_from): launch_run_init takes the place of launch_ctrl_init; launch_round0 fills layer 0; launch_rounds peels until a layer is
 // empty (ctrl->nrounds, ctrl->peeled) or a launch's round limit is reached (nrounds still
 // 0xFFFFFFFF: launch_rounds_again, then launch_rounds again).  generic_shift: edge states of
 // launch_*_r, (round << 3) | position.  Above, a launch per round is as fast or faster: apply
@@ -153,6 +153,9 @@ hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, ui
 // Before launch_rounds on layer r of a claim-list run: the layer's states (all others unclaimed, in
 // st.state, by the caller), the run's place, zeroed barrier words.
 hipError_t launch_rounds_resume(const PeelState& st, uint32_t r, hipStream_t s);
+// Before launch_rounds on layer r behind launch_apply (atomic claims): the run's place; f0: vertices of degree 1
+// before round 0.
+hipError_t launch_rounds_from(const PeelState& st, uint32_t r, uint64_t f0, hipStream_t s);
 hipError_t launch_rounds_again(const PeelState& st, hipStream_t s);
 // All layers of a complete peel of nrounds rounds in one launch, any size; the MPHF's codes and
 // rank samples, or a static function's values u (over the records).  nrounds 0: enqueued behind
@@ -160,7 +163,8 @@ hipError_t launch_rounds_again(const PeelState& st, hipStream_t s);
 // layers: the caller clears the codes or values before, and packs the codes behind.
 // st.sync[1] is zeroed: by launch_run_init, else by launch_sync_zero.
 hipError_t launch_sync_zero(const PeelState& st, hipStream_t s);
-hipError_t launch_copy_ctrl(const Ctrl* ctrl, Ctrl* out, hipStream_t s);
+// layer (nullable): goes to out->layer
+hipError_t launch_copy_ctrl(const Ctrl* ctrl, const unsigned long long* layer, Ctrl* out, hipStream_t s);
 hipError_t launch_mphf_finish(const PeelState& st, uint32_t nrounds, uint64_t* codes, uint64_t* rank, uint32_t* bcount,
                               hipStream_t s);
 hipError_t launch_sf_solve(const PeelState& st, uint32_t nrounds, uint64_t sigma, uint32_t b, hipStream_t s);

@@ -692,6 +692,23 @@ hipError_t launch_rounds_resume(const PeelState& st, uint32_t r, hipStream_t s)
     return hipGetLastError();
 }
 
+// The run's place, for rounds that go on from layer r of launches with atomic claims.
+__global__ void k_rounds_from(const uint64_t* __restrict__ lstart, const unsigned long long* __restrict__ lcount,
+                              Ctrl* ctrl, uint32_t r, uint64_t f0)
+{
+    ctrl->run_lo = lstart[r];
+    ctrl->run_list = lcount[r];
+    ctrl->run_r = r;
+    ctrl->f0 = f0;
+    ctrl->layer0 = lcount[0];
+}
+
+hipError_t launch_rounds_from(const PeelState& st, uint32_t r, uint64_t f0, hipStream_t s)
+{
+    k_rounds_from<<<1, 1, 0, s>>>(st.lstart, st.lcount, st.ctrl, r, f0);
+    return hipGetLastError();
+}
+
 template <bool kGrow>
 static hipError_t launch_rounds_as(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, hipStream_t s)
 {
@@ -727,15 +744,18 @@ hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, ui
                 : launch_rounds_as<false>(st, r, generic_shift, limit, s);
 }
 
-__global__ void k_copy_ctrl(const uint64_t* __restrict__ ctrl, uint64_t* __restrict__ out)
+__global__ void k_copy_ctrl(const uint64_t* __restrict__ ctrl, const unsigned long long* __restrict__ layer,
+                            uint64_t* __restrict__ out)
 {
-    if (threadIdx.x < sizeof(Ctrl) / 8)
-        out[threadIdx.x] = ctrl[threadIdx.x];
+    constexpr uint32_t kWords = sizeof(Ctrl) / 8;
+    static_assert(offsetof(Ctrl, layer) == 8 * (kWords - 1), "the last word");
+    if (threadIdx.x < kWords)
+        out[threadIdx.x] = threadIdx.x == kWords - 1 && layer ? *layer : ctrl[threadIdx.x];
 }
 
-hipError_t launch_copy_ctrl(const Ctrl* ctrl, Ctrl* out, hipStream_t s)
+hipError_t launch_copy_ctrl(const Ctrl* ctrl, const unsigned long long* layer, Ctrl* out, hipStream_t s)
 {
-    k_copy_ctrl<<<1, 64, 0, s>>>(reinterpret_cast<const uint64_t*>(ctrl), reinterpret_cast<uint64_t*>(out));
+    k_copy_ctrl<<<1, 64, 0, s>>>(reinterpret_cast<const uint64_t*>(ctrl), layer, reinterpret_cast<uint64_t*>(out));
     return hipGetLastError();
 }
 
