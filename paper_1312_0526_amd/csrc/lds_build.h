@@ -37,7 +37,8 @@ constexpr uint32_t kQueueNone = 0xFFFFu;
 
 struct __align__(16) LdsBuildState {
     uint32_t tail, err;
-    uint32_t sum[4];  // hinges, claims, hinges of layer 0, hinges of the last round
+    uint32_t peeled[2];  // hinges of try t: peeled[t % 2]
+    uint32_t sum[3];  // of the last try: claims, hinges of layer 0, hinges of the last round
     uint32_t more[3];  // vertices queued in round r: more[r % 3]
     uint32_t bcount[kLdsMaxVertices / 512];
     uint32_t start[kLdsRounds];
@@ -121,7 +122,8 @@ __device__ LdsOutcome lds_build(uint32_t n, uint32_t P, uint64_t seed, uint32_t 
             deg4[v] = 0;
         if (tid == 0) {
             st.tail = st.err = 0;
-            st.sum[0] = st.sum[1] = st.sum[2] = st.sum[3] = 0;
+            st.peeled[t & 1] = 0;  // the try before may still be read
+            st.sum[0] = st.sum[1] = st.sum[2] = 0;
             st.more[0] = 0;
         }
         __syncthreads();
@@ -243,27 +245,30 @@ __device__ LdsOutcome lds_build(uint32_t n, uint32_t P, uint64_t seed, uint32_t 
             mark = next;
             turn = turn1;
         }
+        if (hinges)
+            atomicAdd(&st.peeled[t & 1], hinges);
+        __syncthreads();
+        out.peeled = st.peeled[t & 1];
+        if (out.peeled != n && t + 1 < max_tries)
+            continue;  // of such a try only its failure counts (256 buckets of 100 keys: 278 us, 318 with the sums)
         // the last round's queue, [q0, q1), may hold no hinge: then it is no layer
         for (uint32_t i = q0 + tid; i < q1; i += kBlock)
             if (queue[i] != kQueueNone)
-                st.sum[3] = 1;
+                st.sum[2] = 1;
         if (r) {
             uint32_t layer0 = 0;
             for (uint32_t i = tid; i < start_at(1); i += kBlock)
                 layer0 += queue[i] != kQueueNone;
             if (layer0)
-                atomicAdd(&st.sum[2], layer0);
+                atomicAdd(&st.sum[1], layer0);
         }
-        if (hinges)
-            atomicAdd(&st.sum[0], hinges);
         if (claims)
-            atomicAdd(&st.sum[1], claims);
+            atomicAdd(&st.sum[0], claims);
         __syncthreads();
-        out.rounds = r && !st.sum[3] ? r - 1 : r;
+        out.rounds = r && !st.sum[2] ? r - 1 : r;
         out.frontier = q1;
-        out.peeled = st.sum[0];
-        out.claims = st.sum[1];
-        out.layer0 = st.sum[2];
+        out.claims = st.sum[0];
+        out.layer0 = st.sum[1];
         __syncthreads();
         if (out.peeled == n) {
             out.status = gstart || r < kLdsRounds ? 0 : kLdsTooDense;

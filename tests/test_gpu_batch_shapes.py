@@ -59,3 +59,36 @@ def test_default_grids_use_the_device(mx, buckets, size):
     ref = seconds(1024)
     for block in (256, 512):
         assert seconds(block) < 1.3 * ref, block
+
+
+# most of these fail a few tries, or all that they are given
+@pytest.mark.parametrize("max_tries", [1, 2, 3, 20])
+def test_tries_of_small_buckets(mx, max_tries):
+    import torch
+
+    sizes = [n for n in range(2, 34) for _ in range(12)]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint64)
+    bb = mx.BatchBuild(off, max_tries=max_tries)
+    keys = mx.gen_keys_u64(int(off[-1]), gen_seed=11)
+    bb.run(keys)
+    torch.cuda.synchronize()
+    res = bb.bucket_results()
+    old = mx.get_option("grid")
+    mx.set_option("grid", 4)  # single builds by rounds in device memory
+    try:
+        seen = set()
+        for b in range(len(sizes)):
+            part = keys[int(off[b]):int(off[b + 1])].clone()
+            try:
+                want = mx.mphf_build_u64(part, seed=0, max_tries=max_tries)
+                status = 0
+                assert torch.equal(bb.bucket_codes(b), want["codes"]) and torch.equal(bb.bucket_rank(b), want["rank"])
+            except mx.MphxError as e:
+                want, status = e.info, e.status
+            got = res[b]
+            assert (got["status"], got["tries"], got["seed_used"], got["n_rounds"]) == \
+                (status, want["tries"], want["seed_used"], want["n_rounds"]), (b, sizes[b])
+            seen.add((status, int(got["tries"])))
+        assert len(seen) > 1
+    finally:
+        mx.set_option("grid", old)
