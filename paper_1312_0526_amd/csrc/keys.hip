@@ -5,6 +5,7 @@
 #include "launch.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mphx {
 
@@ -354,24 +355,30 @@ __global__ __launch_bounds__(kHsBlock) void k_hash_str_words(const uint8_t* __re
 // k_hash_str_words takes 256 keys to a block, and a batch that gives each compute unit few blocks pays
 // for its windows and barriers one after the other.  Here four lanes take a key's words in turn, with
 // the loads of 16 words in flight, and one wave finishes the block's 64 keys: three dependent reads
-// (offsets, words, tables) and one barrier.  Words past a key's first kQuadNear are read by the whole wave,
-// key by key, so that a long key does not keep four lanes busy alone.
+// (offsets, words, tables) and one barrier.  Words past a key's first 64 are read by the whole wave, key
+// by key, where that is fewer steps than the longest of its keys would keep four lanes busy for.  A batch
+// of at most 16 keys gives each more lanes, in a kernel of its own (the variable count costs 17% at 196,608
+// keys).  Hashing 16 strings of 1000 bytes took 16.0 us key by key (k_hash_str_words 6.8) and takes 4.4,
+// one of 20,000 by a wave 11.7 (8.5) and 5.0.
 //
 // Lookups of 60-byte strings in a function of 10^7 keys, words and quads: 9.1 and 6.5 us a call at 1,000 keys
 // (an empty launch takes 6.2), 10.1 and 8.2 at 65,536, 19.0 and 18.3 at 200,000, 35.2 and 37.6 at 500,000,
 // where the waves' instructions count and a key's unused lanes with them.
 constexpr uint64_t kQuadMax = 3u << 16;
-constexpr uint32_t kQuadBlock = 256, kQuadKeys = kQuadBlock / 4, kQuadNear = 64;
+constexpr uint32_t kQuadBlock = 256, kQuadKeys = kQuadBlock / 4, kQuadFar = 8, kQuadFew = 16;
 static_assert(kQuadKeys == kWave, "one wave finishes the keys");
 
-template <int kMode>
+template <int kMode, bool kFew>
 __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restrict__ bytes,
                                                           const uint64_t* __restrict__ offs, uint64_t n, uint64_t seed,
                                                           uint64_t P, EvalTables mt)
 {
-    __shared__ ulonglong2 s_digest[kQuadKeys];
-    const uint32_t tid = threadIdx.x, wlane = tid & (kWave - 1), lane = tid & 3;
-    const uint64_t first = (uint64_t)blockIdx.x * kQuadKeys, i = first + tid / 4;
+    __shared__ ulonglong2 s_digest[kQuadKeys], s_part[kQuadBlock / kWave];
+    const uint32_t tid = threadIdx.x, wlane = tid & (kWave - 1);
+    const uint64_t first = (uint64_t)blockIdx.x * kQuadKeys;
+    const uint32_t width = !kFew ? 4u : (n > 4 ? 16u : (n > 1 ? 64u : 256u));
+    const uint32_t key = tid / width, lane = tid & (width - 1), near = 16 * width;  // words
+    const uint64_t i = first + key;
     // the batch's keys are bytes [origin, total), a slice of a larger array perhaps: nothing outside is read
     const uint64_t origin = offs[0], total = offs[n];
     const uint64_t sa = fin(seed + kGamma), sb = fin(seed + 2 * kGamma);
@@ -381,11 +388,12 @@ __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restr
         len = offs[i + 1] - o0;
     }
     uint64_t A = 0, B = 0;
-    // words j, j + step, j + 2 step, j + 3 step of the key of `size` bytes at byte `at`
-    auto add = [&](uint64_t at, uint64_t size, uint64_t j, uint32_t step) {
-        uint64_t w[4];
+    // words j, j + step, ... of the key of `size` bytes at byte `at`, kWords of them
+    auto add = [&](auto words, uint64_t at, uint64_t size, uint64_t j, uint32_t step) {
+        constexpr uint32_t kWords = decltype(words)::value;
+        uint64_t w[kWords];
 #pragma unroll
-        for (uint32_t u = 0; u < 4; u++) {
+        for (uint32_t u = 0; u < kWords; u++) {
             const uint64_t k = j + u * step, p = 8 * k < size ? at + 8 * k : at;
             // eight bytes that end inside the array, and begin there: it has at least eight
             const uint64_t q = min(p, total - 8);
@@ -393,7 +401,7 @@ __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restr
             w[u] >>= 8 * (p - q) & 63;  // an empty key may start at the array's end
         }
 #pragma unroll
-        for (uint32_t u = 0; u < 4; u++) {
+        for (uint32_t u = 0; u < kWords; u++) {
             const uint64_t k = j + u * step;
             if (8 * k < size) {
                 // bytes past the key's end count as zero: shift them out and back
@@ -411,30 +419,64 @@ __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restr
             B += __shfl_xor(B, d, kWave);
         }
     };
+    constexpr std::integral_constant<uint32_t, 4> kSome{};
+    constexpr std::integral_constant<uint32_t, kQuadFar> kMany{};
     if (total - origin >= 8) {
-        const uint64_t near = min<uint64_t>(len, 8 * kQuadNear);
-        for (uint64_t j = lane; 8 * j < near; j += 16)
-            add(o0, near, j, 4);
-        sum(4);
-        for (uint64_t left = __ballot(lane == 0 && len > 8 * kQuadNear); left; left &= left - 1) {
-            const int of = __ffsll((long long)left) - 1;
-            const uint64_t at = wave_bcast64(o0, of), size = wave_bcast64(len, of);
-            const uint64_t a0 = A, b0 = B;
-            A = B = 0;
-            for (uint64_t j = kQuadNear + wlane; 8 * j < size; j += 4 * kWave)
-                add(at, size, j, kWave);
+        const uint64_t some = min<uint64_t>(len, 8 * near);
+        for (uint64_t j = lane; 8 * j < some; j += 4 * width)
+            add(kSome, o0, some, j, width);
+        if (kFew && width >= kWave) {
+            for (uint64_t j = near + lane; 8 * j < len; j += kQuadFar * width)
+                add(kMany, o0, len, j, width);
             sum(kWave);
-            const bool mine = (int)(wlane & ~3u) == of;
-            A = a0 + (mine ? A : 0ull);
-            B = b0 + (mine ? B : 0ull);
+        } else {
+            uint64_t left = __ballot(lane == 0 && len > 8 * near);
+            if (left) {
+                // steps of the wave with all its lanes on one key after the other, and `width` lanes on each
+                const uint32_t words = (uint32_t)min<uint64_t>((len + 7) / 8, 1u << 24), over = words > near ? words - near : 0u;
+                uint32_t far = lane == 0 ? (over + kQuadFar * kWave - 1) / (kQuadFar * kWave) : 0u;
+                uint32_t quad = (over + 4 * width - 1) / (4 * width);
+                for (uint32_t d = kWave / 2; d > 0; d >>= 1) {
+                    far += __shfl_xor(far, d, kWave);
+                    quad = max(quad, __shfl_xor(quad, d, kWave));
+                }
+                if (quad <= far) {
+                    for (uint64_t j = near + lane; 8 * j < len; j += 4 * width)
+                        add(kSome, o0, len, j, width);
+                    left = 0;
+                }
+            }
+            sum(width);
+            for (; left; left &= left - 1) {
+                const int of = __ffsll((long long)left) - 1;
+                const uint64_t at = wave_bcast64(o0, of), size = wave_bcast64(len, of);
+                const uint64_t a0 = A, b0 = B;
+                A = B = 0;
+                for (uint64_t j = near + wlane; 8 * j < size; j += kQuadFar * kWave)
+                    add(kMany, at, size, j, kWave);
+                sum(kWave);
+                const bool mine = (int)(wlane & ~(width - 1)) == of;
+                A = a0 + (mine ? A : 0ull);
+                B = b0 + (mine ? B : 0ull);
+            }
         }
-    } else if (len) {  // every key lies in the array's one word
+    } else if (len && lane == 0) {  // every key lies in the array's one word
         const uint64_t x = key_word(bytes, o0, total) & ((1ull << (8 * len)) - 1);
         A = fin(x ^ sa);
         B = fin(x ^ sb);
     }
+    if (kFew && width > kWave) {  // one key, a share in each wave
+        if (wlane == 0)
+            s_part[tid / kWave] = make_ulonglong2(A, B);
+        __syncthreads();
+        A = B = 0;
+        for (uint32_t q = 0; q < kQuadBlock / kWave; q++) {
+            A += s_part[q].x;
+            B += s_part[q].y;
+        }
+    }
     if (lane == 0)
-        s_digest[tid / 4] = make_ulonglong2(fin(A ^ sa ^ len), fin(B ^ sb ^ len));
+        s_digest[key] = make_ulonglong2(fin(A ^ sa ^ len), fin(B ^ sb ^ len));
     __syncthreads();
     if (tid < kWave && first + tid < n) {
         const ulonglong2 d = s_digest[tid];
@@ -554,7 +596,11 @@ static hipError_t launch_str(const uint8_t* bytes, const uint64_t* offs, uint64_
                              const EvalTables& t, hipStream_t s)
 {
     if (n <= kQuadMax) {
-        k_str_quads<kMode><<<(unsigned)((n + kQuadKeys - 1) / kQuadKeys), kQuadBlock, 0, s>>>(bytes, offs, n, seed, P, t);
+        if (n <= kQuadFew)
+            k_str_quads<kMode, true><<<1, kQuadBlock, 0, s>>>(bytes, offs, n, seed, P, t);
+        else
+            k_str_quads<kMode, false><<<(unsigned)((n + kQuadKeys - 1) / kQuadKeys), kQuadBlock, 0, s>>>(bytes, offs, n,
+                                                                                                      seed, P, t);
         return hipGetLastError();
     }
     const uint64_t chunks = (n + kHsBlock - 1) / kHsBlock;
