@@ -351,13 +351,15 @@ int check_run_errors(const Ctrl& h, uint64_t n, uint64_t rcap, uint32_t r = 3)
 constexpr uint32_t kLaterBatch = 16;
 
 // One launch for all rounds keeps an eighth of the waves in flight that k_apply does, and claims beyond a
-// workgroup's list share one cursor, so in runs of more than kOwnLaunchMin edges the layers of more than
-// kOwnLaunchSize / r^2 edges get launches of their own first, read back two rounds at a time.  All rounds
-// in one launch, all in launches, and both in turn: 6.47, 4.65 and 3.79 ms for 1.6x10^7 u64 keys at gamma 2
-// (half the edges in layer 0), 3.20, 2.85 and 2.11 for 9x10^6; at gamma 1.23 4.59, 5.59 and 4.28, and 2.59,
-// 3.76 and 2.62; 6.39, 5.74 and 5.60 for 6.5x10^6 edges of 8 vertices, whose layer 0 holds some 3x10^5.
-// Below the least run one launch is the best (1.09 ms against 1.19 in turn at 2.5x10^6 keys, gamma 1.23).
-constexpr uint64_t kOwnLaunchMin = 1ull << 22, kOwnLaunchSize = 3ull << 22;
+// workgroup's list share one cursor.  So runs of more than kOwnLaunchMin edges whose layer 0 has more than
+// kOwnLaunchFirst / r^2 make the layers of more than kOwnLaunchLayer / r^2 edges in launches of their own
+// first, read back two rounds at a time.  All rounds in one launch, all in launches, and both in turn:
+// 6.47, 4.65 and 3.82 ms for 1.6x10^7 u64 keys at gamma 2 (half the edges in layer 0), 3.20, 2.85 and 2.18
+// for 9x10^6; 4.59, 5.59 and 4.31 at gamma 1.23 for 1.6x10^7; 6.39, 5.74 and 5.62 for 6.5x10^6 edges of 8
+// vertices.  9x10^6 keys at gamma 1.23, with 2.2x10^6 in layer 0, take 2.62 ms in launches first and 2.59
+// without: hence that line.  Below the least run one launch is the best in general (1.09 ms against 1.19 in turn
+// at 2.5x10^6 keys, gamma 1.23).
+constexpr uint64_t kOwnLaunchMin = 1ull << 22, kOwnLaunchFirst = 5ull << 22, kOwnLaunchLayer = 9ull << 20;
 constexpr uint32_t kHandoverBatch = 2;
 
 // Rounds of a launch each, enqueued in batches; h.layer comes as the edges of layer 0.  With small == 0
@@ -538,9 +540,9 @@ int run_rounds_grid(PeelState& st, uint32_t r, bool generic_shift, Ctrl& h, hipS
         if (!rc) rc = check_run_errors(h, st.n, st.rcap, r);
         if (rc) return rc;
         // every batch of these rounds begins with a layer of more than `small` edges
-        const uint64_t f0 = h.ftail, small = kOwnLaunchSize / (r * r);
+        const uint64_t f0 = h.ftail, small = kOwnLaunchLayer / (r * r);
         HIP_TRY(launch_zero(st.lcount + 1, (st.n / small + 2) * kHandoverBatch * sizeof(unsigned long long), s));
-        rc = run_rounds(st, r, generic_shift, small, h, from, s);
+        if (h.layer > kOwnLaunchFirst / (r * r)) rc = run_rounds(st, r, generic_shift, small, h, from, s);
         if (rc) return rc;
         if (from) HIP_TRY(launch_rounds_from(st, from, f0, s));
     }
