@@ -1321,6 +1321,7 @@ static hipError_t launch_batch_lds(const BatchArgs& a, uint32_t bytes, unsigned 
 
 static hipError_t launch_batch_kernel(const BatchArgs& a, unsigned block, unsigned grid, bool wg_scope, hipStream_t s)
 {
+    grid = (unsigned)std::min<uint64_t>(grid, a.B);  // a workgroup more than buckets has nothing to do
     constexpr int W = __HIP_MEMORY_SCOPE_WORKGROUP, A = __HIP_MEMORY_SCOPE_AGENT;
     if (a.clock) {  // the instantiation that clocks its phases
         switch (block) {
