@@ -101,7 +101,8 @@ def algorithmic_bytes(phase: str, st: dict) -> float:
     if phase == "order":
         return PER_EDGE["order"] * n
     if phase == "assign":
-        return PER_EDGE["assign"] * n
+        # one launch packs and ranks behind the layers in builds of up to 2^24 keys
+        return (PER_EDGE["assign"] + (PER_EDGE["rank"] if st.get("rank_in_assign") else 0.0)) * n
     if phase == "rank":
         return PER_EDGE["rank"] * n
     return 0.0
@@ -152,26 +153,39 @@ def kernel_roofline(phase: str, row: dict, traffic_per_launch) -> dict:
     return out
 
 
-# Phases, the kernels each is made of, and the sources those kernels are compiled from: HBM
-# counters taken on a kernel are reused only while its sources are unchanged.
+# Phases, the kernels each is made of (names and what they begin with), and the sources those kernels
+# are compiled from: HBM counters taken on a kernel are reused only while its sources are unchanged.
+# The rounds are launches of k_apply or all in k_rounds, the layers launches of k_assign_round or
+# all in k_mphf_finish / k_sf_solve; a build may hold both kinds of rounds.
 PHASE_KERNELS = {
     "hash": ("k_hash_str_words", "k_hash_u64_tiles"),
-    "build": ("k_part_accum",),
-    "frontier": ("k_round0",),
-    "apply": ("k_apply",),
+    "build": ("k_part_accum", "k_bins_accum", "k_bins_again"),
+    "frontier": ("k_round0", "k_bins_round0"),
+    "apply": ("k_apply", "k_rounds"),
     "resolve": ("k_claims_resolve",),
     "update": ("k_update_accum",),
-    "assign": ("k_assign_round",),
+    "assign": ("k_assign_round", "k_mphf_finish", "k_sf_solve"),
 }
+NO_PHASE = ("k_rounds_resume", "k_rounds_from")  # bookkeeping between launches, outside the timers
 PHASE_SOURCES = {
     "hash": ("keys.hip",),
-    "build": ("part.hip", "scan.hip"),
-    "frontier": ("peel.hip", "part.hip", "scan.hip"),
-    "apply": ("peel.hip",),
+    "build": ("part.hip", "scan.hip", "bins.hip", "grid.h"),
+    "frontier": ("peel.hip", "part.hip", "scan.hip", "bins.hip", "grid.h"),
+    "apply": ("peel.hip", "rounds.hip", "grid.h"),
     "resolve": ("part.hip", "scan.hip"),
     "update": ("part.hip", "scan.hip"),
-    "assign": ("solve.hip",),
+    "assign": ("solve.hip", "rounds.hip", "grid.h"),
 }
+
+
+def phase_of(kernel: str):
+    """The phase a kernel belongs to, or None."""
+    if kernel in NO_PHASE:
+        return None
+    for phase, prefixes in PHASE_KERNELS.items():
+        if any(kernel.startswith(p) for p in prefixes):
+            return phase
+    return None
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "hbm_counters_{workload}.json")
 
 
@@ -208,6 +222,20 @@ def counters_traffic(workload: str, phase: str):
     if not row or row.get("sources_digest") != sources_digest(phase) or not row.get("launches"):
         return None
     return (row["fetch_bytes"] + row["write_bytes"]) / row["launches"]
+
+
+def counters_missing(workload: str) -> str:
+    """Why counters_step_traffic has nothing to say about a workload."""
+    path = COUNTERS_FILE.format(workload=workload.replace("^", ""))
+    if not os.path.exists(path):
+        return f"{os.path.basename(path)} was never taken"
+    with open(path) as fh:
+        phases = json.load(fh).get("phases", {})
+    lacks = [p for p in PHASE_SOURCES if p not in phases]
+    stale = [p for p in PHASE_SOURCES if p in phases and phases[p].get("sources_digest") != sources_digest(p)]
+    return f"{os.path.basename(path)}: " + "; ".join(
+        [f"phases without a kernel in it: {', '.join(lacks)}"] * bool(lacks) +
+        [f"sources changed since: {', '.join(stale)}"] * bool(stale))
 
 
 def counters_step_traffic(workload: str):
@@ -260,9 +288,9 @@ def summarize_counters(fetch_dir: str, write_dir: str, copy_fetch_dir: str, copy
         doc["kernels"][k] = dict(dispatches=fk.get(k, [0, 0])[1], fetch_bytes=fk.get(k, [0, 0])[0] * f_scale,
                                  write_bytes=wk.get(k, [0, 0])[0] * w_scale)
     # the library times hash, build and frontier as one span per build, the rounds per launch
-    builds = doc["kernels"].get("k_round0", {}).get("dispatches", 1)
-    for ph, prefixes in PHASE_KERNELS.items():
-        ks = [k for k in doc["kernels"] if any(k.startswith(p) for p in prefixes)]
+    builds = max([v["dispatches"] for k, v in doc["kernels"].items() if phase_of(k) == "frontier"], default=1)
+    for ph in PHASE_KERNELS:
+        ks = [k for k in doc["kernels"] if phase_of(k) == ph]
         if not ks:
             continue
         per_launch = ph in ("apply", "assign")
@@ -271,7 +299,7 @@ def summarize_counters(fetch_dir: str, write_dir: str, copy_fetch_dir: str, copy
                                  fetch_bytes=sum(doc["kernels"][k]["fetch_bytes"] for k in ks),
                                  write_bytes=sum(doc["kernels"][k]["write_bytes"] for k in ks))
     # the same build cut in dispatch order: everything between the round-0 kernel and the
-    # first assignment launch is the peel, whichever kernels it is made of
+    # first assignment kernel is the peel, whichever kernels it is made of
     if fw["builds"] and fw["builds"] == ww["builds"]:
         doc["windows"] = dict(builds=fw["builds"], sources_digest={p: sources_digest(p) for p in PEEL_PHASES},
                               **{w: dict(fetch_bytes=fw[w] * f_scale, write_bytes=ww[w] * w_scale)
@@ -327,13 +355,14 @@ def dispatch_rows(d: str) -> list:
 
 def build_windows(rows: list) -> dict:
     """Counter bytes of each build's three windows, averaged over the builds in the run: a
-    build starts at its hashing kernel; the peel window opens at the round-0 kernel and closes
-    at the first assignment launch.  Kernels outside any build (input generators, probes) and
+    build starts at its hashing kernel, or at the tiles that hash u64 keys as they sort them; the peel
+    window opens at the round-0 kernel and closes at the first assignment kernel.  Kernels outside any build (input generators, probes) and
     incomplete builds are left out."""
     sums = {w: 0.0 for w in WINDOWS}
     builds, cur, state = 0, None, None
     for _, name, b in rows:
-        if name.startswith("k_hash_"):
+        starts = name.startswith(("k_hash_", "k_str_quads")) or (name == "k_bins" and state != "hash_build")
+        if starts:
             if cur is not None and state == "assign_rank":
                 builds += 1
                 for w in WINDOWS:
@@ -341,11 +370,11 @@ def build_windows(rows: list) -> dict:
             cur, state = {w: 0.0 for w in WINDOWS}, "hash_build"
         elif cur is None:
             continue
-        elif name.startswith("k_round0") and state == "hash_build":
+        elif phase_of(name) == "frontier" and state == "hash_build":
             state = "peel"
-        elif name.startswith("k_assign_round") and state == "peel":
+        elif phase_of(name) == "assign" and state == "peel":
             state = "assign_rank"
-        elif name.startswith("k_gen_") or name.startswith("k_copy") or name.startswith("k_probe"):
+        elif name.startswith("k_gen_") or name == "k_copy" or name.startswith("k_probe"):
             continue
         cur[state] += b
     if cur is not None and state == "assign_rank":
@@ -1509,6 +1538,7 @@ def main() -> int:
               frontier0=r["frontier0"], claims=r["claims"], lists=lists_from > 0 and n >= (1 << lists_from),
               round0_updates=mx.get_option("update_lists") > 0, layer0=r["layer0"],
               update_deletes=r["update_deletes"], update_records=r["update_records"])
+    st["rank_in_assign"] = not phases.get("rank", (0.0, 0))[1]
     phase_rows = {}
     for name, (ms, launches) in phases.items():
         if launches == 0:
@@ -1537,6 +1567,8 @@ def main() -> int:
                 alg_frac=round(step_alg / (ms_per_step / 1e3) / 1e9 / HBM_PEAK_GBS, 4), peak=HBM_PEAK_GBS,
                 unit="GB/s", traffic=None, traffic_GBps=None, traffic_frac=None)
     step_traffic = counters_step_traffic(cfg["workload"]) if n == cfg["n"] else None
+    if step_traffic is None and n == cfg["n"]:
+        log(f"[bench] no counted traffic: {counters_missing(cfg['workload'])}")
     if step_traffic is not None:
         t_gbs = step_traffic / (ms_per_step / 1e3) / 1e9
         step.update(traffic=round(step_traffic), traffic_GBps=round(t_gbs, 1), traffic_frac=round(t_gbs / HBM_PEAK_GBS, 4),
