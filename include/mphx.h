@@ -659,6 +659,10 @@ MPHX_API int mphx_gen_str_bytes(uint8_t* bytes, const uint64_t* offs, uint64_t n
  *                 most m, the buffers' size).  A round with more claims, or a round 0 with
  *                 more deletes, makes the try start again with atomic claims (the same codes
  *                 either way); a small value exercises that fallback.
+ *   "shared_rounds" b in 0..24 (default 24): runs of at most 2^b edges have all rounds in one launch;
+ *                 larger ones, and all with 0, a launch for each (as far as claim lists do not take
+ *                 them).  With 0 each layer of the assignment has a launch of its own too, and small
+ *                 key sets are not built in one workgroup.  The same outputs either way.
  *   "group_wait"  0..1000 (default 20): microseconds that the first workgroup of a launch which holds
  *                 all rounds, or all layers of the assignment, waits for the rest of the grid
  *                 before the work begins (0: it begins alone).  Workgroups that find room later

@@ -40,6 +40,7 @@ struct Options {
     std::atomic<int> hem_block{1024};  // batched-kernel workgroup size for the HEM split's buckets
     std::atomic<int> hem_grid{0};      // its persistent grid (0 = one workgroup per compute unit)
     std::atomic<int64_t> list_cap{0};  // records a claim-list round may hold (0 = m, the buffers' size)
+    std::atomic<int> shared_rounds{24};      // runs of at most 2^shared_rounds edges share launches (0 = none)
     std::atomic<int> group_wait{20};   // microseconds that a group waits for its whole grid before it
                                        // begins; workgroups that start later join it
     std::atomic<int64_t> group_joins{0};     // workgroups that did so
@@ -333,6 +334,13 @@ unsigned auto_grid(uint64_t work)
     return (unsigned)std::min<uint64_t>(std::max<uint64_t>(b, 64), 1024);
 }
 
+// Runs of at most this many edges: all rounds, and all layers, in one launch each.
+uint64_t shared_max()
+{
+    const int b = g_opt.shared_rounds.load();
+    return b ? std::min<uint64_t>(1ull << b, kRunMaxEdges) : 0;
+}
+
 uint32_t group_wait_ticks() { return 100u * (uint32_t)g_opt.group_wait.load(); }
 
 // Failures that a run's control block reports: round 0's checks, the round limit.
@@ -428,7 +436,7 @@ constexpr uint64_t kRunLayerMax = 1ull << 20, kRunStatesMax = 1ull << 28;
 int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
 {
     const uint64_t upd = (uint64_t)g_opt.update_lists.load();
-    const uint64_t small = st.n <= kRunStatesMax ? std::min<uint64_t>(st.n / 128, kRunLayerMax) : 0;
+    const uint64_t small = shared_max() && st.n <= kRunStatesMax ? std::min<uint64_t>(st.n / 128, kRunLayerMax) : 0;
     const uint64_t large = small + small / 8;
     uint32_t joined = 0;
     bool in_tmp = false;  // round r's claims sit in st.claims_tmp
@@ -527,7 +535,7 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
     return MPHX_OK;
 }
 
-// All rounds of a run of at most kRunMaxEdges edges whose layer 0 is enqueued, then finish()
+// All rounds of a run of at most shared_max() edges whose layer 0 is enqueued, then finish()
 // (enqueued after every launch of rounds; it does nothing while the peel goes on).  One host
 // read unless the peel has more rounds than a launch takes.
 template <class Finish>
@@ -630,6 +638,9 @@ int mphx_set_option(const char* key, int64_t value)
     } else if (!strcmp(key, "list_cap")) {
         if (value < 0) return fail(MPHX_EINVAL, "list_cap must be >= 0");
         g_opt.list_cap = value;
+    } else if (!strcmp(key, "shared_rounds")) {
+        if (value < 0 || value > 24) return fail(MPHX_EINVAL, "shared_rounds must be in 0..24");
+        g_opt.shared_rounds = (int)value;
     } else if (!strcmp(key, "group_wait")) {
         if (value < 0 || value > 1000) return fail(MPHX_EINVAL, "group_wait must be in 0..1000");
         g_opt.group_wait = (int)value;
@@ -661,6 +672,7 @@ int64_t mphx_get_option(const char* key)
     if (!strcmp(key, "batch_claim_lists")) return g_opt.batch_claim_lists;
     if (!strcmp(key, "batch_clock")) return g_opt.batch_clock;
     if (!strcmp(key, "list_cap")) return g_opt.list_cap;
+    if (!strcmp(key, "shared_rounds")) return g_opt.shared_rounds;
     if (!strcmp(key, "group_wait")) return g_opt.group_wait;
     if (!strcmp(key, "group_joins")) return g_opt.group_joins;
     if (!strcmp(key, "list_fallbacks")) return g_opt.list_fallbacks;
@@ -740,8 +752,8 @@ int mphx_peel(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t* order, ui
     st.wait = group_wait_ticks();
     st.rcap = round_cap(n);
 
-    const bool grid_run = n <= kRunMaxEdges;
-    const uint32_t bins = bins_shift(n, m, st.rcap);  // grid_run where not 0
+    const bool grid_run = n <= shared_max();
+    const uint32_t bins = grid_run ? bins_shift(n, m, st.rcap) : 0;
     if (!bins) {
         HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
         HIP_TRY(launch_fill_u32(L.state, n, kUnclaimed, s));
@@ -835,7 +847,7 @@ int mphx_peel_r(const uint32_t* edges, uint64_t n, uint64_t m, uint32_t r, uint3
 
     HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
     HIP_TRY(launch_fill_u32(L.state, n, kUnclaimed, s));
-    const bool grid_run = n <= kRunMaxEdges;
+    const bool grid_run = n <= shared_max();
     HIP_TRY(grid_run ? launch_run_init(st, 1, s) : launch_zero(L.lcount, (st.rcap + 2) * sizeof(unsigned long long), s));
     if (!grid_run) HIP_TRY(launch_ctrl_init(L.ctrl, L.lstart, s));
     {
@@ -1147,16 +1159,17 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
     layout_mphf(c, n, m, lists, L, sf != nullptr);
     uint32_t t0 = 0;  // the first try that is left to do
     const int pb = g_opt.part_build.load();  // <= 32
-    const uint32_t bins = pb > 1 && !lists ? bins_shift(n, m, round_cap(n)) : 0;
+    const bool shared = n <= shared_max();
+    const uint32_t bins = pb > 1 && !lists && shared ? bins_shift(n, m, round_cap(n)) : 0;
     const bool part = !bins && pb > 0 && n >= (1ull << pb);
-    if (!sf && !lists && !part && g_opt.grid.load() == 0 && small_build_fits(n, m)) {
+    if (!sf && !lists && !part && shared && g_opt.grid.load() == 0 && small_build_fits(n, m)) {
         int rc = small_build(k, n, seed, P, max_tries, codes, rank, L, s, info, t0);
         if (rc || t0 == 0) return rc;
         if (t0 == kFirstTryAgain) t0 = 0;
     }
     // every value below sigma: checked first, or by the first try where that reads the host back only
     // once (20 us of 1040 at 2x10^6 keys)
-    const bool check_later = !lists && n <= kRunMaxEdges;
+    const bool check_later = !lists && shared;
     auto bad_value = [&] {
         return fail(MPHX_EINVAL, "a value is not below sigma = %llu", (unsigned long long)sf->sigma);
     };
@@ -1207,7 +1220,7 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
         uint64_t sd = seed + t;
         if (!part && !bins)
             HIP_TRY(launch_zero(L.rec, m * sizeof(uint64_t), s));
-        grid_run = !st.lists && n <= kRunMaxEdges;
+        grid_run = !st.lists && shared;
         if (grid_run) {
             HIP_TRY(launch_run_init(st, bins ? bins_zero_words(m, bins) : 1, s));
             if (sf && check_later && t == 0)
@@ -1312,7 +1325,7 @@ int mphf_build(const KeySrc& k, uint64_t n, uint64_t seed, uint32_t gnum, uint32
             info->layer0 = l0;
         }
         const uint64_t bytes = m * (sf ? sf_elem_bytes(mphx_sf_bits(sf->sigma)) : 1);
-        if (bytes <= kSolveGridMaxBytes) {
+        if (shared_max() && bytes <= kSolveGridMaxBytes) {
             st.grid_cap = (unsigned)g_opt.grid.load();
             HIP_TRY(launch_sync_zero(st, s));
             HIP_TRY(launch_zero(L.rec, bytes, s));
