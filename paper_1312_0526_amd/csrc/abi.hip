@@ -547,12 +547,14 @@ int run_rounds_grid(PeelState& st, uint32_t r, bool generic_shift, Ctrl& h, hipS
         int rc = read_ctrl(st.ctrl, h, s, st.lcount);
         if (!rc) rc = check_run_errors(h, st.n, st.rcap, r);
         if (rc) return rc;
-        // every batch of these rounds begins with a layer of more than `small` edges
-        const uint64_t f0 = h.ftail, small = kOwnLaunchLayer / (r * r);
-        HIP_TRY(launch_zero(st.lcount + 1, (st.n / small + 2) * kHandoverBatch * sizeof(unsigned long long), s));
-        if (h.layer > kOwnLaunchFirst / (r * r)) rc = run_rounds(st, r, generic_shift, small, h, from, s);
-        if (rc) return rc;
-        if (from) HIP_TRY(launch_rounds_from(st, from, f0, s));
+        if (h.layer > kOwnLaunchFirst / (r * r)) {
+            // every batch of these rounds begins with a layer of more than `small` edges
+            const uint64_t f0 = h.ftail, small = kOwnLaunchLayer / (r * r);
+            HIP_TRY(launch_zero(st.lcount + 1, (st.n / small + 2) * kHandoverBatch * sizeof(unsigned long long), s));
+            rc = run_rounds(st, r, generic_shift, small, h, from, s);
+            if (rc) return rc;
+            HIP_TRY(launch_rounds_from(st, from, f0, s));
+        }
     }
     st.grid_cap = (unsigned)g_opt.grid.load();
     for (;;) {
