@@ -196,7 +196,7 @@ MPHX_API int mphx_mphf_lookup_str(const uint64_t* codes, const uint64_t* rank, u
  *   ws     (dev) at least mphx_sf_workspace_bytes(n, ...) bytes, 256-byte aligned.
  *   info   as for the MPHF (P and seed_used are needed for lookups).
  * Errors: as mphx_mphf_build_*, plus MPHX_EINVAL for sigma outside [1, 2^32] or a value not
- * below sigma (checked on the device before any try).  Synchronises the stream.
+ * below sigma (checked on the device, before or with the first try).  Synchronises the stream.
  * mphx_sf_lookup_*: out[i] = f(key i) (dev, n uint64).  Enqueue only.
  * --------------------------------------------------------------------------------------- */
 MPHX_API uint32_t mphx_sf_bits(uint64_t sigma);
@@ -586,7 +586,11 @@ MPHX_API int mphx_gen_str_bytes(uint8_t* bytes, const uint64_t* offs, uint64_t n
 /* ---------------------------------------------------------------------------------------
  * Tuning and diagnostics.
  * mphx_set_option / mphx_get_option (process-wide):
- *   "grid"        blocks per launch of the peeling kernels (0 = automatic).  Up to 2^24 edges
+ *   "grid"        blocks per launch of the peeling kernels (0 = automatic).  With 0,
+ *                 mphx_mphf_build_* makes key sets whose graph fits in one workgroup's LDS (about
+ *                 26,000 keys at gamma 1.23; with "part_build" and "claim_lists" above their number)
+ *                 in a single launch of one workgroup, retries included; any other value
+ *                 turns that off, several times the time for such sets.  Up to 2^24 edges
  *                 all rounds share one launch of at most 256 512-thread blocks (automatic: one
  *                 per 4096 to 40960 edges), as do the assignment's layers up to 2^30 bytes of
  *                 vertex values; above, and for large layers of more than 2^22 edges, each round is a
@@ -671,6 +675,11 @@ MPHX_API int mphx_gen_str_bytes(uint8_t* bytes, const uint64_t* offs, uint64_t n
  *   "list_fallbacks" (read; set only to 0 to reset) tries redone with atomic claims after
  *                 a list overflowed, over the process.
  * Returns MPHX_EINVAL for an unknown key or value.
+ *
+ * A phase is what was launched for it: the hashing of u64 keys that sorts them into buckets as it
+ * goes counts as "hash"; the layers of MPHF builds of at most 2^24 keys, packing and ranking included,
+ * as "assign" ("rank" stays 0 there); all of a build in one workgroup as "apply", but for the hashing of its
+ * strings where that has a launch of its own.
  *
  * mphx_phase_times copies the accumulated per-phase kernel time (ms) and launch counts of
  * the calling thread (phases: hash, build, frontier, apply, resolve, assign, rank, order, other,

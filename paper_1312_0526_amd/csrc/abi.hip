@@ -571,7 +571,7 @@ int run_rounds_grid(PeelState& st, uint32_t r, bool generic_shift, Ctrl& h, hipS
         if (rc || h.nrounds != 0xFFFFFFFFu) return rc;
         grow = h.run_r == from;  // no round was made: the device is busy
         from = h.run_r;
-        HIP_TRY(launch_rounds_again(st, s));
+        HIP_TRY(launch_sync_zero(st, s));
     }
 }
 

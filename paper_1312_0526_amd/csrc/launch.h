@@ -137,7 +137,7 @@ hipError_t launch_apply(const PeelState& st, uint32_t r, bool hinge_in_slot, App
 // Runs of at most kRunMaxEdges edges (rounds.hip) peel in one launch, large layers at their beginning
 // aside (launch_rounds_from): launch_run_init takes the place of launch_ctrl_init; launch_round0 fills layer 0; launch_rounds peels until a layer is
 // empty (ctrl->nrounds, ctrl->peeled) or a launch's round limit is reached (nrounds still
-// 0xFFFFFFFF: launch_rounds_again, then launch_rounds again).  generic_shift: edge states of
+// 0xFFFFFFFF: launch_sync_zero, then launch_rounds again).  generic_shift: edge states of
 // launch_*_r, (round << 3) | position.  Above, a launch per round is as fast or faster: apply
 // launches against one launch took 2450 and 1832 us at 10^7 keys, 5760 and 5743 at 3x10^7, 11574
 // and 14285 at 6x10^7, where the rounds are bound by the device atomics and many small
@@ -156,7 +156,6 @@ hipError_t launch_rounds_resume(const PeelState& st, uint32_t r, hipStream_t s);
 // Before launch_rounds on layer r behind launch_apply (atomic claims): the run's place; f0: vertices of degree 1
 // before round 0.
 hipError_t launch_rounds_from(const PeelState& st, uint32_t r, uint64_t f0, hipStream_t s);
-hipError_t launch_rounds_again(const PeelState& st, hipStream_t s);
 // All layers of a complete peel of nrounds rounds in one launch, any size; the MPHF's codes and
 // rank samples, or a static function's values u (over the records).  nrounds 0: enqueued behind
 // launch_rounds before its outcome is known, does nothing after an incomplete peel; else only the

@@ -60,7 +60,8 @@ struct LdsOutcome {
     uint32_t rounds, peeled, frontier0, frontier, claims, layer0;  // of the last try
 };
 
-// Appends v0 and / or v1 (want1 and want2 of every active lane) with one LDS atomic per wave.
+// Room for each active lane's entries, want1 and want2 of them, with one LDS atomic per wave: where the
+// lane's first goes.
 __device__ __forceinline__ uint32_t queue_reserve(uint32_t* tail, bool want1, bool want2)
 {
     const uint64_t b1 = __ballot(want1), b2 = __ballot(want2);

@@ -759,8 +759,6 @@ hipError_t launch_copy_ctrl(const Ctrl* ctrl, const unsigned long long* layer, C
     return hipGetLastError();
 }
 
-hipError_t launch_rounds_again(const PeelState& st, hipStream_t s) { return launch_sync_zero(st, s); }
-
 hipError_t launch_mphf_finish(const PeelState& st, uint32_t nrounds, uint64_t* codes, uint64_t* rank, uint32_t* bcount,
                               hipStream_t s)
 {
