@@ -109,11 +109,8 @@ __global__ __launch_bounds__(kBlock) void k_bins(Src src, BinArgs a, uint32_t wi
     uint32_t* const lst = reinterpret_cast<uint32_t*>(buf + kTile);  // width + 1: counts, then their prefix
     uint32_t* const delta = lst + width + 1;                         // run's place in its bucket - place in buf
     __shared__ uint32_t wtot[kBlock / kWave];
-    __shared__ bool s_full;
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const uint64_t t0 = (uint64_t)blockIdx.x * kTile;
-    if (tid == 0)
-        s_full = ag_load(a.full) != 0;
     uint32_t v[kPer][3];
     {
         typename Src::Raw x[kPer];
@@ -134,8 +131,6 @@ __global__ __launch_bounds__(kBlock) void k_bins(Src src, BinArgs a, uint32_t wi
         for (uint32_t j = tid; j <= width; j += kBlock)
             lst[j] = 0;
         __syncthreads();
-        if (s_full)
-            return;  // k_bins_again needs the edges alone
         uint32_t rk[kPer];
 #pragma unroll
         for (uint32_t q = 0; q < kPer; q++)
@@ -173,7 +168,7 @@ __global__ __launch_bounds__(kBlock) void k_bins(Src src, BinArgs a, uint32_t wi
                 const uint32_t at = atomicAdd(&a.cursor[b0 + j], c);
                 delta[j] = at - lst[j];
                 if (at + c > a.length(b0 + j) + a.extra)
-                    ag_store(a.full, 1);
+                    *a.full = 1;
             }
         }
 #pragma unroll
