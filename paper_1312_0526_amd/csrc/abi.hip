@@ -359,14 +359,15 @@ int check_run_errors(const Ctrl& h, uint64_t n, uint64_t rcap, uint32_t r = 3)
 constexpr uint32_t kLaterBatch = 16;
 
 // One launch for all rounds keeps an eighth of the waves in flight that k_apply does, and claims beyond a
-// workgroup's list share one cursor.  So runs of more than kOwnLaunchMin edges whose layer 0 has more than
-// kOwnLaunchFirst / r^2 make the layers of more than kOwnLaunchLayer / r^2 edges in launches of their own
-// first, read back two rounds at a time.  All rounds in one launch, all in launches, and both in turn:
-// 6.47, 4.65 and 3.82 ms for 1.6x10^7 u64 keys at gamma 2 (half the edges in layer 0), 3.20, 2.85 and 2.18
-// for 9x10^6; 4.59, 5.59 and 4.31 at gamma 1.23 for 1.6x10^7; 6.39, 5.74 and 5.62 for 6.5x10^6 edges of 8
-// vertices.  9x10^6 keys at gamma 1.23, with 2.2x10^6 in layer 0, take 2.62 ms in launches first and 2.59
-// without: hence that line.  Below the least run one launch is the best in general (1.09 ms against 1.19 in turn
-// at 2.5x10^6 keys, gamma 1.23).
+// workgroup's list share one cursor.  So in runs of more than kOwnLaunchMin edges a layer 0 of more than
+// kOwnLaunchFirst / r^2 is left alone by that launch, and it and the layers behind it of more than
+// kOwnLaunchLayer / r^2 edges get launches of their own, read back two rounds at a time, before the one
+// launch takes the rest.  All rounds in one launch, all in launches, and both in turn: 6.47, 4.65 and
+// 3.80 ms for 1.6x10^7 u64 keys at gamma 2 (half the edges in layer 0), 3.20, 2.85 and 2.16 for 9x10^6;
+// 4.59, 5.59 and 4.29 at gamma 1.23 for 1.6x10^7; 6.39, 5.74 and 5.59 for 6.5x10^6 edges of 8 vertices.  9x10^6
+// keys at gamma 1.23, with 2.2x10^6 in layer 0, take 2.62 ms in launches first and 2.59 without: hence that
+// line.  Below the least run one launch is the best in general (1.09 ms against 1.19 in turn at 2.5x10^6
+// keys, gamma 1.23).
 constexpr uint64_t kOwnLaunchMin = 1ull << 22, kOwnLaunchFirst = 5ull << 22, kOwnLaunchLayer = 9ull << 20;
 constexpr uint32_t kHandoverBatch = 2;
 
@@ -466,7 +467,7 @@ int run_rounds_lists(PeelState& st, Ctrl& h, uint64_t* peeled, hipStream_t s)
                 for (uint32_t from = r;;) {
                     {
                         Timed t(PH_APPLY, s);
-                        HIP_TRY(launch_rounds(st, 3, false, large, grow, s));
+                        HIP_TRY(launch_rounds(st, 3, false, large, ~0ull, grow, s));
                     }
                     int rc = read_ctrl(st.ctrl, h, s);
                     if (!rc) rc = check_run_errors(h, st.n, st.rcap);
@@ -543,34 +544,33 @@ int run_rounds_grid(PeelState& st, uint32_t r, bool generic_shift, Ctrl& h, hipS
 {
     uint32_t joined = 0, from = 0;
     bool grow = false;
-    if (st.n > kOwnLaunchMin) {
+    uint64_t first = st.n > kOwnLaunchMin ? kOwnLaunchFirst / (r * r) : ~0ull;
+    for (;;) {
+        {
+            Timed t(PH_APPLY, s);
+            HIP_TRY(launch_rounds(st, r, generic_shift, ~0ull, first, grow, s));
+        }
+        HIP_TRY(finish());
         int rc = read_ctrl(st.ctrl, h, s, st.lcount);
-        if (!rc) rc = check_run_errors(h, st.n, st.rcap, r);
         if (rc) return rc;
-        if (h.layer > kOwnLaunchFirst / (r * r)) {
+        g_opt.group_joins += h.joined - joined;
+        joined = h.joined;
+        rc = check_run_errors(h, st.n, st.rcap, r);
+        if (rc || h.nrounds != 0xFFFFFFFFu) return rc;
+        const bool large = from == 0 && h.run_r == 0 && h.layer > first;
+        first = ~0ull;
+        if (large) {
             // every batch of these rounds begins with a layer of more than `small` edges
             const uint64_t f0 = h.ftail, small = kOwnLaunchLayer / (r * r);
             HIP_TRY(launch_zero(st.lcount + 1, (st.n / small + 2) * kHandoverBatch * sizeof(unsigned long long), s));
             rc = run_rounds(st, r, generic_shift, small, h, from, s);
             if (rc) return rc;
             HIP_TRY(launch_rounds_from(st, from, f0, s));
+            st.grid_cap = (unsigned)g_opt.grid.load();
+        } else {
+            grow = h.run_r == from;  // no round was made: the device is busy
+            from = h.run_r;
         }
-    }
-    st.grid_cap = (unsigned)g_opt.grid.load();
-    for (;;) {
-        {
-            Timed t(PH_APPLY, s);
-            HIP_TRY(launch_rounds(st, r, generic_shift, ~0ull, grow, s));
-        }
-        HIP_TRY(finish());
-        int rc = read_ctrl(st.ctrl, h, s);
-        if (rc) return rc;
-        g_opt.group_joins += h.joined - joined;
-        joined = h.joined;
-        rc = check_run_errors(h, st.n, st.rcap, r);
-        if (rc || h.nrounds != 0xFFFFFFFFu) return rc;
-        grow = h.run_r == from;  // no round was made: the device is busy
-        from = h.run_r;
         HIP_TRY(launch_sync_zero(st, s));
     }
 }

@@ -148,8 +148,10 @@ hipError_t launch_run_init(const PeelState& st, uint64_t zero_words, hipStream_t
 // A layer of more than limit edges ends the launch too, all of it in the slots (edge ids, hinges in
 // the states) and its size in lcount.
 // Without `grow` the launch does nothing (ctrl->nrounds and run_r as before) unless its whole grid finds room
-// at once; with it the group begins smaller and grows.
-hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, bool grow, hipStream_t s);
+// at once; with it the group begins smaller and grows.  Nothing either where layer 0 is to come and has
+// more than `first` edges.
+hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, uint64_t first, bool grow,
+                         hipStream_t s);
 // Before launch_rounds on layer r of a claim-list run: the layer's states (all others unclaimed, in
 // st.state, by the caller), the run's place, zeroed barrier words.
 hipError_t launch_rounds_resume(const PeelState& st, uint32_t r, hipStream_t s);

@@ -82,6 +82,7 @@ struct RoundsArgs {
     GridSync* sync;
     uint64_t n, P, rcap;
     uint64_t limit;  // a layer beyond it ends the launch
+    uint64_t first;  // a layer 0 beyond it: nothing is done
     uint32_t wait;   // grid_join's
     const uint32_t* vin;  // static functions: see PeelState
     uint32_t* vout;
@@ -365,8 +366,8 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(RoundsArgs a)
     __shared__ RoundsShared sh;
     // a degree above 255 (see k_round0) or a bad edge: nothing may be read off the records, and every
     // workgroup leaves.  (A launch that goes on from a later round has passed this.)
-    if (a.ctrl->run_r == 0 &&
-        ((a.ctrl->err & (kErrDegree | kErrBadEdge)) || a.ctrl->degsum != (uint64_t)kR * a.n))
+    if (a.ctrl->run_r == 0 && ((a.ctrl->err & (kErrDegree | kErrBadEdge)) || a.ctrl->degsum != (uint64_t)kR * a.n ||
+                               a.lcount[0] > a.first))
         return;
     Grid g;
     if (!grid_join<kGrow>(a.sync, g, sh.join, a.wait))
@@ -710,10 +711,11 @@ hipError_t launch_rounds_from(const PeelState& st, uint32_t r, uint64_t f0, hipS
 }
 
 template <bool kGrow>
-static hipError_t launch_rounds_as(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, hipStream_t s)
+static hipError_t launch_rounds_as(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, uint64_t first,
+                                   hipStream_t s)
 {
     const RoundsArgs a{st.rec, st.edges, st.state, st.slots, st.lstart, st.lcount, st.ctrl, st.sync,
-                       st.n,   st.P,     st.rcap,  limit,    st.wait,   st.vin,    st.vout};
+                       st.n,   st.P,     st.rcap,  limit,    first,      st.wait,   st.vin,    st.vout};
     const unsigned g = run_grid(st);
     if (st.tripartite) {
         if (r != 3 || generic_shift) return hipErrorInvalidValue;
@@ -738,10 +740,11 @@ static hipError_t launch_rounds_as(const PeelState& st, uint32_t r, bool generic
     return hipGetLastError();
 }
 
-hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, bool grow, hipStream_t s)
+hipError_t launch_rounds(const PeelState& st, uint32_t r, bool generic_shift, uint64_t limit, uint64_t first, bool grow,
+                         hipStream_t s)
 {
-    return grow ? launch_rounds_as<true>(st, r, generic_shift, limit, s)
-                : launch_rounds_as<false>(st, r, generic_shift, limit, s);
+    return grow ? launch_rounds_as<true>(st, r, generic_shift, limit, first, s)
+                : launch_rounds_as<false>(st, r, generic_shift, limit, first, s);
 }
 
 __global__ void k_copy_ctrl(const uint64_t* __restrict__ ctrl, const unsigned long long* __restrict__ layer,
