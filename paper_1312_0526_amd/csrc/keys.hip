@@ -379,14 +379,17 @@ __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restr
     const uint32_t width = !kFew ? 4u : (n > 4 ? 16u : (n > 1 ? 64u : 256u));
     const uint32_t key = tid / width, lane = tid & (width - 1), near = 16 * width;  // words
     const uint64_t i = first + key;
-    // the batch's keys are bytes [origin, total), a slice of a larger array perhaps: nothing outside is read
-    const uint64_t origin = offs[0], total = offs[n];
+    const uint64_t total = offs[n];
     const uint64_t sa = fin(seed + kGamma), sb = fin(seed + 2 * kGamma);
-    uint64_t o0 = origin, len = 0;
+    uint64_t o0 = 0, len = 0;
     if (i < n) {
         o0 = offs[i];
         len = offs[i + 1] - o0;
     }
+    // The batch may be a slice of a larger array of which nothing else is there: lanes without a word read the
+    // offsets, and a key in the last seven bytes is left to dword reads at the end.
+    const bool tail = len && (total < 8 || o0 > total - 8);
+    const uint64_t size0 = tail ? 0 : len;
     uint64_t A = 0, B = 0;
     // words j, j + step, ... of the key of `size` bytes at byte `at`, kWords of them
     auto add = [&](auto words, uint64_t at, uint64_t size, uint64_t j, uint32_t step) {
@@ -394,11 +397,10 @@ __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restr
         uint64_t w[kWords];
 #pragma unroll
         for (uint32_t u = 0; u < kWords; u++) {
-            const uint64_t k = j + u * step, p = 8 * k < size ? at + 8 * k : at;
-            // eight bytes that end inside the array, and begin there: it has at least eight
-            const uint64_t q = min(p, total - 8);
-            __builtin_memcpy(&w[u], bytes + q, 8);
-            w[u] >>= 8 * (p - q) & 63;  // an empty key may start at the array's end
+            // eight bytes that end inside the array, and do not begin before the key
+            const uint64_t k = j + u * step, p = at + 8 * k, q = min(p, total - 8);
+            __builtin_memcpy(&w[u], 8 * k < size ? bytes + q : reinterpret_cast<const uint8_t*>(offs), 8);
+            w[u] >>= 8 * (p - q) & 63;
         }
 #pragma unroll
         for (uint32_t u = 0; u < kWords; u++) {
@@ -421,46 +423,45 @@ __global__ __launch_bounds__(kQuadBlock) void k_str_quads(const uint8_t* __restr
     };
     constexpr std::integral_constant<uint32_t, 4> kSome{};
     constexpr std::integral_constant<uint32_t, kQuadFar> kMany{};
-    if (total - origin >= 8) {
-        const uint64_t some = min<uint64_t>(len, 8 * near);
-        for (uint64_t j = lane; 8 * j < some; j += 4 * width)
-            add(kSome, o0, some, j, width);
-        if (kFew && width >= kWave) {
-            for (uint64_t j = near + lane; 8 * j < len; j += kQuadFar * width)
-                add(kMany, o0, len, j, width);
-            sum(kWave);
-        } else {
-            uint64_t left = __ballot(lane == 0 && len > 8 * near);
-            if (left) {
-                // steps of the wave with all its lanes on one key after the other, and `width` lanes on each
-                const uint32_t words = (uint32_t)min<uint64_t>((len + 7) / 8, 1u << 24), over = words > near ? words - near : 0u;
-                uint32_t far = lane == 0 ? (over + kQuadFar * kWave - 1) / (kQuadFar * kWave) : 0u;
-                uint32_t quad = (over + 4 * width - 1) / (4 * width);
-                for (uint32_t d = kWave / 2; d > 0; d >>= 1) {
-                    far += __shfl_xor(far, d, kWave);
-                    quad = max(quad, __shfl_xor(quad, d, kWave));
-                }
-                if (quad <= far) {
-                    for (uint64_t j = near + lane; 8 * j < len; j += 4 * width)
-                        add(kSome, o0, len, j, width);
-                    left = 0;
-                }
+    const uint64_t some = min<uint64_t>(size0, 8 * near);
+    for (uint64_t j = lane; 8 * j < some; j += 4 * width)
+        add(kSome, o0, some, j, width);
+    if (kFew && width >= kWave) {
+        for (uint64_t j = near + lane; 8 * j < size0; j += kQuadFar * width)
+            add(kMany, o0, size0, j, width);
+        sum(kWave);
+    } else {
+        uint64_t left = __ballot(lane == 0 && size0 > 8 * near);
+        if (left) {
+            // steps of the wave with all its lanes on one key after the other, and `width` lanes on each
+            const uint32_t words = (uint32_t)min<uint64_t>((size0 + 7) / 8, 1u << 24), over = words > near ? words - near : 0u;
+            uint32_t far = lane == 0 ? (over + kQuadFar * kWave - 1) / (kQuadFar * kWave) : 0u;
+            uint32_t quad = (over + 4 * width - 1) / (4 * width);
+            for (uint32_t d = kWave / 2; d > 0; d >>= 1) {
+                far += __shfl_xor(far, d, kWave);
+                quad = max(quad, __shfl_xor(quad, d, kWave));
             }
-            sum(width);
-            for (; left; left &= left - 1) {
-                const int of = __ffsll((long long)left) - 1;
-                const uint64_t at = wave_bcast64(o0, of), size = wave_bcast64(len, of);
-                const uint64_t a0 = A, b0 = B;
-                A = B = 0;
-                for (uint64_t j = near + wlane; 8 * j < size; j += kQuadFar * kWave)
-                    add(kMany, at, size, j, kWave);
-                sum(kWave);
-                const bool mine = (int)(wlane & ~(width - 1)) == of;
-                A = a0 + (mine ? A : 0ull);
-                B = b0 + (mine ? B : 0ull);
+            if (quad <= far) {
+                for (uint64_t j = near + lane; 8 * j < size0; j += 4 * width)
+                    add(kSome, o0, size0, j, width);
+                left = 0;
             }
         }
-    } else if (len && lane == 0) {  // every key lies in the array's one word
+        sum(width);
+        for (; left; left &= left - 1) {
+            const int of = __ffsll((long long)left) - 1;
+            const uint64_t at = wave_bcast64(o0, of), size = wave_bcast64(size0, of);
+            const uint64_t a0 = A, b0 = B;
+            A = B = 0;
+            for (uint64_t j = near + wlane; 8 * j < size; j += kQuadFar * kWave)
+                add(kMany, at, size, j, kWave);
+            sum(kWave);
+            const bool mine = (int)(wlane & ~(width - 1)) == of;
+            A = a0 + (mine ? A : 0ull);
+            B = b0 + (mine ? B : 0ull);
+        }
+    }
+    if (tail && lane == 0) {
         const uint64_t x = key_word(bytes, o0, total) & ((1ull << (8 * len)) - 1);
         A = fin(x ^ sa);
         B = fin(x ^ sb);
